@@ -408,8 +408,9 @@ typedef struct fem_batch_plan fem_batch_plan;
 fem_status fem_batch_plan_create(const fem_mesh_desc* meshes, int n_mesh, int dtype,
                                  fem_batch_plan** out);
 /* Launch shape of the persistent kernel: waves per workgroup (1, 2, 4, 8;
- * one element per lane, so a tile is 64*waves_per_block elements) and
- * workgroups per compute unit (0 = one workgroup per tile). Defaults 8 and 0.
+ * a tile is 64*waves_per_block lanes of one element each, or of 16 bytes of
+ * every row each when the batch is large) and
+ * workgroups per compute unit (0 = one workgroup per tile). Defaults 4 and 0.
  * Drops a recorded graph (capture again). Synchronizes the device. */
 fem_status fem_batch_plan_set_launch(fem_batch_plan* plan, int waves_per_block, int blocks_per_cu);
 /* Sweep the launch shapes above (waves per workgroup 1, 2, 4, 8; workgroups
@@ -458,7 +459,8 @@ fem_status fem_batch_run_noalloc(const fem_mesh_desc* meshes, int n_mesh, int dt
 typedef struct fem_tuning {
     int strategy;        /* enum fem_strategy (each strategy names the operations it serves) */
     int vec;             /* elements per lane: RESIDUAL and BACKWARD read 1, 2 or 4
-                          * consecutive elements per vector access; GEOMETRY,
+                          * consecutive elements per vector access, at any count
+                          * and word alignment; GEOMETRY,
                           * RESIDUAL_MESH and RESIDUAL_GATHER (1, 2, 4) give each lane that
                           * many elements 64 apart, to overlap their dependent vertex
                           * gathers; the P2 and element-matrix ops take 1 */
@@ -469,7 +471,9 @@ typedef struct fem_tuning {
 
 /* The configuration used for (op, dim, physics, rule, dtype), for every
  * coefficient space: the last one set or tuned in this process, else a
- * built-in default. */
+ * built-in default. The built-in default of RESIDUAL and BACKWARD takes more
+ * elements per lane, that of the element matrices four waves, where rows
+ * start off the 128-byte lines. */
 fem_status fem_get_tuning(int op, int dim, int physics, int rule, int dtype, fem_tuning* out);
 /* Override the configuration for (op, dim, physics, rule, dtype) in this process. */
 fem_status fem_set_tuning(int op, int dim, int physics, int rule, int dtype, const fem_tuning* t);

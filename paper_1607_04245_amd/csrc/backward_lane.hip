@@ -11,65 +11,49 @@
 
 namespace femq {
 
-template <int DIM, int PHYS, int RULE, typename Real, int V>
+template <int DIM, int PHYS, int RULE, typename Real, int V, bool STREAM_OUT>
 __global__ void __launch_bounds__(512)
-backward_lane_kernel(int64_t n, const Real* __restrict__ inv_j, const Real* __restrict__ det_j,
+backward_lane_kernel(int64_t n, int order, const Real* __restrict__ inv_j, const Real* __restrict__ det_j,
                      const Real* __restrict__ u, const Real* __restrict__ coef,
                      const Real* __restrict__ w, Real* __restrict__ du, Real* __restrict__ dcoef) {
     using E = Elem<DIM, PHYS, RULE>;
-    const int64_t nchunk = n / V;
+    const int64_t nchunk = (n + V - 1) / V;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     const bool want_du = du != nullptr;
     const bool want_dc = dcoef != nullptr;
-    for (int64_t ch = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; ch < nchunk; ch += stride) {
-        const int64_t e0 = ch * V;
-        Real rij[E::NG][V], rdj[V], rw[E::NBT][V];
-#pragma unroll
-        for (int f = 0; f < E::NG; ++f) ld_row<Real, V>(inv_j + f * n + e0, rij[f]);
-        ld_row<Real, V>(det_j + e0, rdj);
-#pragma unroll
-        for (int f = 0; f < E::NBT; ++f) ld_row<Real, V>(w + f * n + e0, rw[f]);
-        if (want_du) {
-            Real rcf[E::NCQ][V], rr[E::NBT][V];
-#pragma unroll
-            for (int f = 0; f < E::NCQ; ++f) ld_row<Real, V>(coef + f * n + e0, rcf[f]);
-#pragma unroll
-            for (int v = 0; v < V; ++v) {
-                Real ij[E::NG], ww[E::NBT], cf[E::NCQ], r[E::NBT];
-#pragma unroll
-                for (int f = 0; f < E::NG; ++f) ij[f] = rij[f][v];
-#pragma unroll
-                for (int f = 0; f < E::NBT; ++f) ww[f] = rw[f][v];
-#pragma unroll
-                for (int f = 0; f < E::NCQ; ++f) cf[f] = rcf[f][v];
-                element_residual<DIM, PHYS, RULE, Real>(ij, rdj[v], ww, cf, r);
-#pragma unroll
-                for (int f = 0; f < E::NBT; ++f) rr[f][v] = r[f];
+    for (int64_t ch = row_block(order) * blockDim.x + threadIdx.x; ch < nchunk; ch += stride) {
+        for_chunk<V>(ch * V, n, [&](auto width, int64_t e) {
+            constexpr int W = decltype(width)::value;
+            Real rij[E::NG][W], rdj[1][W], rw[E::NBT][W];
+            load_rows_v<E::NG>(inv_j, n, e, rij);
+            load_rows_v<1>(det_j, n, e, rdj);
+            load_rows_v<E::NBT>(w, n, e, rw);
+            if (want_du) {
+                Real rcf[E::NCQ][W], rr[E::NBT][W];
+                load_rows_v<E::NCQ>(coef, n, e, rcf);
+                lane_residual<DIM, PHYS, RULE, Real>(rij, rdj, rw, rcf, rr);
+                store_rows_v<E::NBT, STREAM_OUT>(du, n, e, rr);
             }
+            if (want_dc) {
+                Real ru[E::NBT][W], rd[E::NCQ][W];
+                load_rows_v<E::NBT>(u, n, e, ru);
 #pragma unroll
-            for (int f = 0; f < E::NBT; ++f) st_row<Real, V>(du + f * n + e0, rr[f]);
-        }
-        if (want_dc) {
-            Real ru[E::NBT][V], rd[E::NCQ][V];
+                for (int v = 0; v < W; ++v) {
+                    Real ij[E::NG], uu[E::NBT], ww[E::NBT], d[E::NCQ];
 #pragma unroll
-            for (int f = 0; f < E::NBT; ++f) ld_row<Real, V>(u + f * n + e0, ru[f]);
+                    for (int f = 0; f < E::NG; ++f) ij[f] = rij[f][v];
 #pragma unroll
-            for (int v = 0; v < V; ++v) {
-                Real ij[E::NG], uu[E::NBT], ww[E::NBT], d[E::NCQ];
+                    for (int f = 0; f < E::NBT; ++f) {
+                        uu[f] = ru[f][v];
+                        ww[f] = rw[f][v];
+                    }
+                    element_dcoef<DIM, PHYS, RULE, Real>(ij, rdj[0][v], uu, ww, d);
 #pragma unroll
-                for (int f = 0; f < E::NG; ++f) ij[f] = rij[f][v];
-#pragma unroll
-                for (int f = 0; f < E::NBT; ++f) {
-                    uu[f] = ru[f][v];
-                    ww[f] = rw[f][v];
+                    for (int f = 0; f < E::NCQ; ++f) rd[f][v] = d[f];
                 }
-                element_dcoef<DIM, PHYS, RULE, Real>(ij, rdj[v], uu, ww, d);
-#pragma unroll
-                for (int f = 0; f < E::NCQ; ++f) rd[f][v] = d[f];
+                store_rows_v<E::NCQ, STREAM_OUT>(dcoef, n, e, rd);
             }
-#pragma unroll
-            for (int f = 0; f < E::NCQ; ++f) st_row<Real, V>(dcoef + f * n + e0, rd[f]);
-        }
+        });
     }
 }
 
@@ -82,21 +66,17 @@ static hipError_t launch_v(const BackwardArgs& a, const Launch& l) {
     const Real* w = static_cast<const Real*>(a.w);
     Real* du = static_cast<Real*>(a.du);
     Real* dc = static_cast<Real*>(a.dcoef);
+    auto go = [&](auto vec_c) {
+        constexpr int V = decltype(vec_c)::value;
+        const auto k = l.stream_out ? backward_lane_kernel<DIM, PHYS, RULE, Real, V, true>
+                               : backward_lane_kernel<DIM, PHYS, RULE, Real, V, false>;
+        hipLaunchKernelGGL(k, dim3(l.grid), dim3(l.block), 0, l.stream, a.n, l.order, ij, dj, u, cf, w, du, dc);
+    };
     switch (l.vec) {
-    case 1:
-        hipLaunchKernelGGL((backward_lane_kernel<DIM, PHYS, RULE, Real, 1>), dim3(l.grid), dim3(l.block), 0,
-                           l.stream, a.n, ij, dj, u, cf, w, du, dc);
-        break;
-    case 2:
-        hipLaunchKernelGGL((backward_lane_kernel<DIM, PHYS, RULE, Real, 2>), dim3(l.grid), dim3(l.block), 0,
-                           l.stream, a.n, ij, dj, u, cf, w, du, dc);
-        break;
-    case 4:
-        hipLaunchKernelGGL((backward_lane_kernel<DIM, PHYS, RULE, Real, 4>), dim3(l.grid), dim3(l.block), 0,
-                           l.stream, a.n, ij, dj, u, cf, w, du, dc);
-        break;
-    default:
-        return hipErrorInvalidValue;
+    case 1: go(std::integral_constant<int, 1>()); break;
+    case 2: go(std::integral_constant<int, 2>()); break;
+    case 4: go(std::integral_constant<int, 4>()); break;
+    default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }

@@ -146,11 +146,10 @@ static TuneKey tune_key(int op, int dim, int phys, int rule, int dtype) {
 }
 
 // Built-in launch configurations: the winners of the autotuner's sweep on
-// one MI355X for the benchmark workloads (one element per lane was within a
-// few percent of the best everywhere; wider accesses raise register pressure
-// without adding bandwidth); other combinations use the robust middle choice.
+// one MI355X for the benchmark workloads; other combinations use the robust
+// middle choice. p1_tuning and set_rows refine them by count and alignment.
 static fem_tuning default_tuning(int op, int dim, int phys, int rule, int dtype) {
-    fem_tuning t{FEM_STRATEGY_LANE, 1, 2, 0};
+    const fem_tuning t{FEM_STRATEGY_LANE, 1, 4, 0};  // RESIDUAL, BACKWARD: whole lines (p1_tuning)
     const bool f32 = dtype == FEM_F32;
     if (op == FEM_OP_GEOMETRY) return fem_tuning{FEM_STRATEGY_LANE, 4, 4, 0};
     if (op == FEM_OP_JACOBIAN || op == FEM_OP_JACOBIAN_P2) {  // store-bound: more waves for the large matrices
@@ -163,17 +162,16 @@ static fem_tuning default_tuning(int op, int dim, int phys, int rule, int dtype)
     // the lane kernel with both timed on a warmed-up GPU.)
     if (op == FEM_OP_RESIDUAL_P3 || op == FEM_OP_BACKWARD_P3) return fem_tuning{FEM_STRATEGY_LANE, 1, dim == 3 ? 1 : 4, 0};
     if (op == FEM_OP_JACOBIAN_P3) return fem_tuning{FEM_STRATEGY_LANE, 1, 4, 0};
-    if (one_per_lane_op(op)) return fem_tuning{FEM_STRATEGY_LANE, 1, 2, 0};
+    // P2 (the remaining ops of one element per lane): FP32 streams best with
+    // four waves (2D elasticity, 2^22 triangles: 116 us with two, 110 with four),
+    // FP64 with one (3D elasticity adjoint, 1,000,001 tets: 270, 287 with two).
+    if (one_per_lane_op(op)) return fem_tuning{FEM_STRATEGY_LANE, 1, f32 ? 4 : 1, 0};
     if (op == FEM_OP_RESIDUAL_GATHER) return fem_tuning{FEM_STRATEGY_LANE, 2, 1, 0};
     if (op == FEM_OP_RESIDUAL_MESH) {
         if (phys == FEM_LAPLACE && f32) return fem_tuning{FEM_STRATEGY_LANE, 1, 1, 8};
         if (phys == FEM_ELASTICITY && f32) return fem_tuning{FEM_STRATEGY_LANE, 2, 2, 0};
         return fem_tuning{FEM_STRATEGY_LANE, 2, 1, 0};
     }
-    const bool deg2 = rule != FEM_RULE_CENTROID;
-    if (deg2 && phys == FEM_LAPLACE && dim == 3) t = f32 ? fem_tuning{0, 1, 2, 16} : fem_tuning{0, 1, 1, 0};
-    if (deg2 && phys == FEM_ELASTICITY && dim == 2) t = f32 ? fem_tuning{0, 1, 4, 4} : fem_tuning{0, 1, 4, 0};
-    if (deg2 && phys == FEM_ELASTICITY && dim == 3) t = f32 ? fem_tuning{0, 1, 4, 2} : fem_tuning{0, 1, 1, 2};
     return t;
 }
 
@@ -236,17 +234,57 @@ void put_tuning(int op, int dim, int phys, int rule, int dtype, const fem_tuning
     g_tune[tune_key(op, dim, phys, rule, dtype)] = t;
 }
 
-// Largest vector width <= want such that every row of every array starts on
-// a vec-word boundary.
-static int usable_vec(int want, int64_t n, size_t word, const void* const* ptrs, int nptr) {
-    for (int v = want; v > 1; v >>= 1) {
-        if (n % v) continue;
-        bool ok = true;
-        for (int i = 0; i < nptr; ++i)
-            if (ptrs[i] && (reinterpret_cast<uintptr_t>(ptrs[i]) % (v * word))) ok = false;
-        if (ok) return v;
-    }
-    return 1;
+// Whether t is the built-in configuration, which the row rules below refine
+// by size and alignment; any other one is used as it is.
+static bool is_default(const fem_tuning& t, int op, int dim, int phys, int rule, int dtype) {
+    const fem_tuning d = default_tuning(op, dim, phys, rule, dtype);
+    return t.strategy == d.strategy && t.vec == d.vec && t.waves_per_block == d.waves_per_block &&
+           t.blocks_per_cu == d.blocks_per_cu;
+}
+
+// Words per element that an order-k residual reads and writes as rows: the
+// geometry, n_closure closures (u, w, R, du) and n_coef coefficient sets.
+static int64_t row_words(int dim, int phys, int rule, int space, int order, int n_closure, int n_coef_sets) {
+    const int nb = order == 1 ? dim + 1 : order == 2 ? (dim + 1) * (dim + 2) / 2 : (dim == 2 ? 10 : 20);
+    const int nc = phys == FEM_ELASTICITY ? dim : 1, m = phys == FEM_ELASTICITY ? 2 : 1;
+    const int nq = rule == FEM_RULE_CENTROID ? 1 : rule == FEM_RULE_TRI6 ? 6 : rule == FEM_RULE_TET11 ? 11 : dim + 1;
+    const int nw = space == FEM_COEF_QUAD ? nq : space == FEM_COEF_P1 ? dim + 1 : 1;
+    return dim * dim + 1 + (int64_t)n_closure * nb * nc + (int64_t)n_coef_sets * m * nw;
+}
+
+// Stores and workgroup order of a launch over `bytes` of rows; whole: every
+// output row starts on a 128-byte line. One MI355X, us, bare rows or kernels:
+//  - Rows at odd words: plain stores, XCD by XCD. A line at a wave's edge is
+//    written in two parts; plain stores let the parts meet in the L2 that the
+//    neighbouring workgroups then share. 144 FP32 rows written: 1.8-2.4 TB/s
+//    streamed in launch order, 4.5 this way (whole lines 5.1-5.4); P2 3D
+//    elasticity FP32, 2,000,001 tets: 207 and 147.
+//  - Whole lines below 192 MiB, which the 256 MB last-level cache can hold:
+//    plain stores, runs of 16 workgroups per XCD. P1 3D Laplacian FP32, 2^20
+//    tets (92 MB): 16.4, and 18.2 XCD by XCD; P2 (172 MB): 29.7, and 32.1 as
+//    streamed in launch order.
+//  - Whole lines from 192 MiB up: XCD by XCD, each XCD streaming its own
+//    eighth of every row. P1 2D Laplacian FP64 (470 MB) 86 in launch order,
+//    75 this way; P1 3D elasticity FP64 (705 MB) 127 and 112.
+//  - and from 512 MB up with streaming stores: P1 3D elasticity FP64 112, 121
+//    plain; P2 3D elasticity FP32 (772 MB) 135, 146 plain; but at 352 MB (P1
+//    3D elasticity FP32) 59 streaming, 56 plain.
+static void set_rows(Launch& l, bool whole, int64_t bytes) {
+    l.stream_out = whole && bytes >= (int64_t)512 << 20;
+    l.order = !whole || bytes >= (int64_t)192 << 20 ? kOrderXcd : kOrderRuns;
+}
+
+// Configuration of the P1 lane kernels for n elements. Rows at odd words take
+// 16 bytes per lane (four FP32 or two FP64 elements), so that a wave shares 2
+// of its 9 lines with its neighbours and not 2 of 3 (FP32), as long as that
+// leaves two waves per SIMD: P1 3D Laplacian FP32, 1,500,001 tets, 25.1 us with
+// one element per lane, 23.0 with four (whole lines 23.4); its adjoint 34.4
+// and 31.0.
+static fem_tuning p1_tuning(const fem_tuning& t, int dtype, int64_t n, bool whole) {
+    if (whole) return t;
+    int vec = dtype == FEM_F32 ? 4 : 2;
+    while (vec > 1 && n < (int64_t)vec * 64 * 2048) vec >>= 1;
+    return fem_tuning{FEM_STRATEGY_LANE, vec, 1, 0};
 }
 
 static Launch make_launch(const fem_tuning& t, int64_t work_items, int vec, hipStream_t s) {
@@ -343,6 +381,7 @@ fem_status fem_geometry(int dim, int64_t n_elem, int64_t n_vert, const double* c
     if (!coords || !conn || !inv_j || !det_j) { set_error("fem_geometry: NULL array"); return FEM_ERR_INVALID_ARG; }
     const fem_tuning t = get_tuning(FEM_OP_GEOMETRY, dim, 0, 0, out_dtype);
     Launch l = make_tile_launch(t, n_elem, static_cast<hipStream_t>(stream));
+    l.stream_out = whole_lines(n_elem, out_dtype == FEM_F32 ? 4 : 8, {inv_j, det_j});
     hipError_t e = launch_geometry(dim, out_dtype, n_elem, n_vert, coords, conn, inv_j, det_j, counts, l);
     return e == hipSuccess ? FEM_OK : hip_fail(e, "fem_geometry launch");
 }
@@ -361,7 +400,6 @@ fem_status fem_integrate_residual(int dim, int physics, int rule, int coef_space
     }
     fem_tuning t = get_tuning(FEM_OP_RESIDUAL, dim, physics, rule, dtype);
     ResidualArgs a{n_elem, inv_j, det_j, u, coef, elem_vec};
-    const size_t word = dtype == FEM_F32 ? 4 : 8;
     hipError_t e;
     if (t.strategy == FEM_STRATEGY_TRANSPOSE) {
         int threads = transpose_block_threads(dim, physics, rule, coef_space, dtype, t.waves_per_block);
@@ -377,9 +415,11 @@ fem_status fem_integrate_residual(int dim, int physics, int rule, int coef_space
         Launch l = make_launch(t, (n_elem + 15) / 16 * 64, 1, static_cast<hipStream_t>(stream));
         e = launch_residual_shuffle(dim, physics, rule, coef_space, dtype, a, l);
     } else {
-        const void* ptrs[5] = {inv_j, det_j, u, coef, elem_vec};
-        int vec = usable_vec(t.vec, n_elem, word, ptrs, 5);
-        Launch l = make_launch(t, n_elem / vec, vec, static_cast<hipStream_t>(stream));
+        const size_t word = dtype == FEM_F32 ? 4 : 8;
+        const bool whole = whole_lines(n_elem, word, {elem_vec});
+        if (is_default(t, FEM_OP_RESIDUAL, dim, physics, rule, dtype)) t = p1_tuning(t, dtype, n_elem, whole);
+        Launch l = make_launch(t, (n_elem + t.vec - 1) / t.vec, t.vec, static_cast<hipStream_t>(stream));
+        set_rows(l, whole, n_elem * (int64_t)word * row_words(dim, physics, rule, coef_space, 1, 2, 1));
         e = launch_residual_lane(dim, physics, rule, coef_space, dtype, a, l);
     }
     return e == hipSuccess ? FEM_OK : hip_fail(e, "fem_integrate_residual launch");
@@ -402,6 +442,7 @@ fem_status fem_integrate_residual_mesh(int dim, int physics, int rule, int coef_
     const fem_tuning t = get_tuning(FEM_OP_RESIDUAL_MESH, dim, physics, rule, dtype);
     MeshArgs a{n_elem, n_vert, coords, conn, u, coef, elem_vec, inv_j, det_j, counts};
     Launch l = make_tile_launch(t, n_elem, static_cast<hipStream_t>(stream));
+    l.stream_out = whole_lines(n_elem, dtype == FEM_F32 ? 4 : 8, {elem_vec, inv_j, det_j});
     hipError_t e = t.strategy == FEM_STRATEGY_DEDUP ? launch_residual_dedup(dim, physics, rule, coef_space, dtype, a, l)
                                                     : launch_residual_mesh(dim, physics, rule, coef_space, dtype, a, l);
     return e == hipSuccess ? FEM_OK : hip_fail(e, "fem_integrate_residual_mesh launch");
@@ -424,6 +465,7 @@ fem_status fem_integrate_residual_gather(int dim, int physics, int rule, int coe
     const fem_tuning t = get_tuning(FEM_OP_RESIDUAL_GATHER, dim, physics, rule, dtype);
     MeshArgs a{n_elem, n_vert, coords, conn, u_vertex, coef, elem_vec, inv_j, det_j, counts};
     Launch l = make_tile_launch(t, n_elem, static_cast<hipStream_t>(stream));
+    l.stream_out = whole_lines(n_elem, dtype == FEM_F32 ? 4 : 8, {elem_vec, inv_j, det_j});
     hipError_t e = launch_residual_gather(dim, physics, rule, coef_space, dtype, a, l);
     return e == hipSuccess ? FEM_OK : hip_fail(e, "fem_integrate_residual_gather launch");
 }
@@ -442,10 +484,13 @@ fem_status fem_integrate_residual_backward(int dim, int physics, int rule, int c
     }
     fem_tuning t = get_tuning(FEM_OP_BACKWARD, dim, physics, rule, dtype);
     const size_t word = dtype == FEM_F32 ? 4 : 8;
-    const void* ptrs[7] = {inv_j, det_j, w, du ? coef : nullptr, du, dcoef ? u : nullptr, dcoef};
-    int vec = usable_vec(t.vec, n_elem, word, ptrs, 7);
+    const bool whole = whole_lines(n_elem, word, {du, dcoef});
+    if (is_default(t, FEM_OP_BACKWARD, dim, physics, rule, dtype)) t = p1_tuning(t, dtype, n_elem, whole);
     BackwardArgs a{n_elem, inv_j, det_j, u, coef, w, du, dcoef};
-    Launch l = make_launch(t, n_elem / vec, vec, static_cast<hipStream_t>(stream));
+    Launch l = make_launch(t, (n_elem + t.vec - 1) / t.vec, t.vec, static_cast<hipStream_t>(stream));
+    set_rows(l, whole, n_elem * (int64_t)word *
+                           row_words(dim, physics, rule, coef_space, 1, (du ? 2 : 1) + (dcoef ? 1 : 0),
+                                     (du ? 1 : 0) + (dcoef ? 1 : 0)));
     hipError_t e = launch_backward_lane(dim, physics, rule, coef_space, dtype, a, l);
     return e == hipSuccess ? FEM_OK : hip_fail(e, "fem_integrate_residual_backward launch");
 }
@@ -465,6 +510,9 @@ fem_status fem_integrate_residual_p2(int dim, int physics, int rule, int coef_sp
     const fem_tuning t = get_tuning(FEM_OP_RESIDUAL_P2, dim, physics, rule, dtype);
     ResidualArgs a{n_elem, inv_j, det_j, u, coef, elem_vec};
     Launch l = make_launch(t, n_elem, 1, static_cast<hipStream_t>(stream));
+    const size_t word = dtype == FEM_F32 ? 4 : 8;
+    set_rows(l, whole_lines(n_elem, word, {elem_vec}),
+             n_elem * (int64_t)word * row_words(dim, physics, rule, coef_space, 2, 2, 1));
     hipError_t e = launch_residual_p2(dim, physics, rule, coef_space, dtype, a, l);
     return e == hipSuccess ? FEM_OK : hip_fail(e, "fem_integrate_residual_p2 launch");
 }
@@ -497,6 +545,13 @@ fem_status fem_integrate_residual_p3(int dim, int physics, int rule, int coef_sp
         e = launch_residual_p3_comp(coef_space, dtype, a, l);
     } else {
         Launch l = make_launch(t, n_elem, 1, static_cast<hipStream_t>(stream));
+        const size_t word = dtype == FEM_F32 ? 4 : 8;
+        set_rows(l, whole_lines(n_elem, word, {elem_vec}),
+                 n_elem * (int64_t)word * row_words(dim, physics, rule, coef_space, 3, 2, 1));
+        if (whole_lines(n_elem, word, {elem_vec})) {
+            l.stream_out = true;
+            l.order = kOrderLaunch;
+        }
         e = launch_residual_p3(dim, physics, coef_space, dtype, a, l);
     }
     return e == hipSuccess ? FEM_OK : hip_fail(e, "fem_integrate_residual_p3 launch");
@@ -517,6 +572,9 @@ fem_status fem_integrate_residual_p2_backward(int dim, int physics, int rule, in
     const fem_tuning t = get_tuning(FEM_OP_BACKWARD_P2, dim, physics, rule, dtype);
     BackwardArgs a{n_elem, inv_j, det_j, u, coef, w, du, dcoef};
     Launch l = make_launch(t, n_elem, 1, static_cast<hipStream_t>(stream));
+    const size_t word = dtype == FEM_F32 ? 4 : 8;
+    set_rows(l, whole_lines(n_elem, word, {du, dcoef}),
+             n_elem * (int64_t)word * row_words(dim, physics, rule, coef_space, 2, (du ? 2 : 1) + (dcoef ? 1 : 0), (du ? 1 : 0) + (dcoef ? 1 : 0)));
     hipError_t e = launch_backward_p2(dim, physics, rule, coef_space, dtype, a, l);
     return e == hipSuccess ? FEM_OK : hip_fail(e, "fem_integrate_residual_p2_backward launch");
 }
@@ -536,6 +594,13 @@ fem_status fem_integrate_residual_p3_backward(int dim, int physics, int rule, in
     const fem_tuning t = get_tuning(FEM_OP_BACKWARD_P3, dim, physics, rule, dtype);
     BackwardArgs a{n_elem, inv_j, det_j, u, coef, w, du, dcoef};
     Launch l = make_launch(t, n_elem, 1, static_cast<hipStream_t>(stream));
+    const size_t word = dtype == FEM_F32 ? 4 : 8;
+    set_rows(l, whole_lines(n_elem, word, {du, dcoef}),
+             n_elem * (int64_t)word * row_words(dim, physics, rule, coef_space, 3, (du ? 2 : 1) + (dcoef ? 1 : 0), (du ? 1 : 0) + (dcoef ? 1 : 0)));
+    if (whole_lines(n_elem, word, {du, dcoef})) {
+        l.stream_out = true;
+        l.order = kOrderLaunch;
+    }
     hipError_t e = launch_backward_p3(dim, physics, coef_space, dtype, a, l);
     return e == hipSuccess ? FEM_OK : hip_fail(e, "fem_integrate_residual_p3_backward launch");
 }
@@ -553,9 +618,16 @@ fem_status fem_integrate_jacobian(int dim, int physics, int rule, int coef_space
         return FEM_ERR_INVALID_ARG;
     }
     const int op = order == 1 ? FEM_OP_JACOBIAN : order == 2 ? FEM_OP_JACOBIAN_P2 : FEM_OP_JACOBIAN_P3;
-    const fem_tuning t = get_tuning(op, dim, physics, rule, dtype);
+    fem_tuning t = get_tuning(op, dim, physics, rule, dtype);
+    // Rows at odd words: four waves per workgroup, XCD by XCD. Whole lines in
+    // launch order (P1 3D elasticity FP64, 400,000 tets: 113 us, 115 us XCD by
+    // XCD; at 400,001 tets 184 us streaming in launch order, 145 us this way).
+    const bool whole = whole_lines(n_elem, dtype == FEM_F32 ? 4 : 8, {elem_mat});
+    if (!whole && is_default(t, op, dim, physics, rule, dtype)) t = fem_tuning{FEM_STRATEGY_LANE, 1, 4, 0};
     JacobianArgs a{n_elem, inv_j, det_j, coef, elem_mat};
     Launch l = make_launch(t, n_elem, 1, static_cast<hipStream_t>(stream));
+    l.stream_out = whole;
+    l.order = whole ? kOrderLaunch : kOrderXcd;
     hipError_t e = order == 3 ? launch_jacobian_p3(dim, physics, coef_space, dtype, a, l)
                               : launch_jacobian(dim, physics, order, rule, coef_space, dtype, a, l);
     return e == hipSuccess ? FEM_OK : hip_fail(e, "fem_integrate_jacobian launch");

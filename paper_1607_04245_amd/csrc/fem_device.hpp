@@ -10,7 +10,10 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "fem.h"
+#include "fem_internal.hpp"
 #include "fem_scheme.hpp"
 
 namespace femq {
@@ -20,6 +23,19 @@ namespace femq {
 // the operation sequence of an element is the same in every kernel.
 __device__ __forceinline__ float fmadd(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 __device__ __forceinline__ double fmadd(double a, double b, double c) { return __builtin_fma(a, b, c); }
+
+// ------------------------------------------------------------- row access --
+// Element rows are read and written once. Loads stream (nontemporal);
+// stores stream or not as the launch says (Launch::stream_out: set_rows has
+// the rule and its measurements).
+template <typename T>
+__device__ __forceinline__ T row_ld(const T* p) { return __builtin_nontemporal_load(p); }
+
+template <bool STREAM_OUT, typename T>
+__device__ __forceinline__ void row_st(T v, T* p) {
+    if constexpr (STREAM_OUT) __builtin_nontemporal_store(v, p);
+    else *p = v;
+}
 
 // ---------------------------------------------------------------- traits --
 
@@ -434,7 +450,7 @@ __device__ __forceinline__ int finish_geometry(bool ok, double& det, double (&in
 // Geometry of one element from its vertices, classified, and stored (rounded
 // once to the output type) when valid: the epilogue of every kernel that
 // writes the geometry alone.
-template <int DIM, typename Out>
+template <int DIM, bool STREAM_OUT, typename Out>
 __device__ __forceinline__ void geometry_finish(bool valid, int64_t e, int64_t n, bool ok,
                                                 const double (&x)[DIM + 1][DIM], Out* __restrict__ inv_j,
                                                 Out* __restrict__ det_j, int& ndeg, int& npoor) {
@@ -448,8 +464,8 @@ __device__ __forceinline__ void geometry_finish(bool valid, int64_t e, int64_t n
         for (int k = 0; k < DIM; ++k)
 #pragma unroll
             for (int i = 0; i < DIM; ++i)
-                __builtin_nontemporal_store(static_cast<Out>(inv[k][i]), inv_j + (int64_t)(k * DIM + i) * n + e);
-        __builtin_nontemporal_store(static_cast<Out>(det), det_j + e);
+                row_st<STREAM_OUT>(static_cast<Out>(inv[k][i]), inv_j + (int64_t)(k * DIM + i) * n + e);
+        row_st<STREAM_OUT>(static_cast<Out>(det), det_j + e);
     }
 }
 
@@ -477,6 +493,30 @@ __device__ __forceinline__ void block_tile_range(int64_t n_tiles, int64_t& begin
     end = (L + 1) * n_tiles / gridDim.x;
 }
 
+// The workgroup's place in the element range (Launch::order): its own
+// number, numbered XCD by XCD, or with runs of kRun consecutive places dealt
+// to the XCDs in turn.
+__device__ __forceinline__ int64_t row_block(int order) {
+    if (order == kOrderXcd) return xcd_logical_block(blockIdx.x, gridDim.x);
+    const int64_t b = blockIdx.x;
+    constexpr int64_t span = kXcds * kRun;
+    if (order == kOrderLaunch || b >= gridDim.x / span * span) return b;
+    return b / span * span + b % kXcds * kRun + b % span / kXcds;
+}
+
+// Words e of N consecutive rows.
+template <int N, typename Real>
+__device__ __forceinline__ void load_rows(const Real* __restrict__ p, int64_t n, int64_t e, Real (&x)[N]) {
+#pragma unroll
+    for (int f = 0; f < N; ++f) x[f] = row_ld(p + f * n + e);
+}
+
+template <int N, bool STREAM_OUT, typename Real>
+__device__ __forceinline__ void store_rows(Real* __restrict__ p, int64_t n, int64_t e, const Real (&x)[N]) {
+#pragma unroll
+    for (int f = 0; f < N; ++f) row_st<STREAM_OUT>(x[f], p + f * n + e);
+}
+
 // Adds per-wave sums of the two counters (every lane of the wave active).
 __device__ __forceinline__ void add_counts(int32_t* counts, int ndeg, int npoor) {
     if (counts == nullptr) return;
@@ -493,38 +533,82 @@ __device__ __forceinline__ void add_counts(int32_t* counts, int ndeg, int npoor)
 
 // --------------------------------------------------- vector memory access --
 
+// Word-aligned vectors: rows start on any word, and global memory accesses of
+// any width need no more than that on gfx950.
 template <typename Real, int V> struct VecT;
 template <> struct VecT<float, 1> { typedef float T; };
-template <> struct VecT<float, 2> { typedef float T __attribute__((ext_vector_type(2))); };
-template <> struct VecT<float, 4> { typedef float T __attribute__((ext_vector_type(4))); };
+template <> struct VecT<float, 2> { typedef float T __attribute__((ext_vector_type(2), aligned(4))); };
+template <> struct VecT<float, 4> { typedef float T __attribute__((ext_vector_type(4), aligned(4))); };
 template <> struct VecT<double, 1> { typedef double T; };
-template <> struct VecT<double, 2> { typedef double T __attribute__((ext_vector_type(2))); };
-template <> struct VecT<double, 4> { typedef double T __attribute__((ext_vector_type(4))); };
+template <> struct VecT<double, 2> { typedef double T __attribute__((ext_vector_type(2), aligned(8))); };
+template <> struct VecT<double, 4> { typedef double T __attribute__((ext_vector_type(4), aligned(8))); };
 
-// Load V consecutive elements of one SoA row (p must be aligned to V words).
-template <typename Real, int V>
-__device__ __forceinline__ void ld_row(const Real* __restrict__ p, Real (&out)[V]) {
+// Words e .. e+V-1 of N consecutive rows: x[f][v].
+template <int N, typename Real, int V>
+__device__ __forceinline__ void load_rows_v(const Real* __restrict__ p, int64_t n, int64_t e, Real (&x)[N][V]) {
     typedef typename VecT<Real, V>::T T;
-    const T x = __builtin_nontemporal_load(reinterpret_cast<const T*>(p));
-    if constexpr (V == 1) {
-        out[0] = x;
-    } else {
 #pragma unroll
-        for (int v = 0; v < V; ++v) out[v] = x[v];
+    for (int f = 0; f < N; ++f) {
+        const T t = __builtin_nontemporal_load(reinterpret_cast<const T*>(p + f * n + e));
+        if constexpr (V == 1) {
+            x[f][0] = t;
+        } else {
+#pragma unroll
+            for (int v = 0; v < V; ++v) x[f][v] = t[v];
+        }
     }
 }
 
-template <typename Real, int V>
-__device__ __forceinline__ void st_row(Real* __restrict__ p, const Real (&in)[V]) {
+template <int N, bool STREAM_OUT, typename Real, int V>
+__device__ __forceinline__ void store_rows_v(Real* __restrict__ p, int64_t n, int64_t e, const Real (&x)[N][V]) {
     typedef typename VecT<Real, V>::T T;
-    T x;
-    if constexpr (V == 1) {
-        x = in[0];
-    } else {
 #pragma unroll
-        for (int v = 0; v < V; ++v) x[v] = in[v];
+    for (int f = 0; f < N; ++f) {
+        T t;
+        if constexpr (V == 1) {
+            t = x[f][0];
+        } else {
+#pragma unroll
+            for (int v = 0; v < V; ++v) t[v] = x[f][v];
+        }
+        T* dst = reinterpret_cast<T*>(p + f * n + e);
+        if constexpr (STREAM_OUT) __builtin_nontemporal_store(t, dst);
+        else *dst = t;
     }
-    __builtin_nontemporal_store(x, reinterpret_cast<T*>(p));
+}
+
+// element_residual of W elements whose words are laid out as load_rows_v
+// leaves them.
+template <int DIM, int PHYS, int RULE, typename Real, int W>
+__device__ __forceinline__ void lane_residual(const Real (&rij)[Elem<DIM, PHYS, RULE>::NG][W], const Real (&rdj)[1][W],
+                                              const Real (&ru)[Elem<DIM, PHYS, RULE>::NBT][W],
+                                              const Real (&rcf)[Elem<DIM, PHYS, RULE>::NCQ][W],
+                                              Real (&rr)[Elem<DIM, PHYS, RULE>::NBT][W]) {
+    using E = Elem<DIM, PHYS, RULE>;
+#pragma unroll
+    for (int v = 0; v < W; ++v) {
+        Real ij[E::NG], uu[E::NBT], cf[E::NCQ], r[E::NBT];
+#pragma unroll
+        for (int f = 0; f < E::NG; ++f) ij[f] = rij[f][v];
+#pragma unroll
+        for (int f = 0; f < E::NBT; ++f) uu[f] = ru[f][v];
+#pragma unroll
+        for (int f = 0; f < E::NCQ; ++f) cf[f] = rcf[f][v];
+        element_residual<DIM, PHYS, RULE, Real>(ij, rdj[0][v], uu, cf, r);
+#pragma unroll
+        for (int f = 0; f < E::NBT; ++f) rr[f][v] = r[f];
+    }
+}
+
+// Runs body(integral constant W, e) on the elements e0 .. e0+V-1 below n: all
+// V at once, or one by one in the lane whose elements run past the end.
+template <int V, typename Body>
+__device__ __forceinline__ void for_chunk(int64_t e0, int64_t n, const Body& body) {
+    if (V == 1 || e0 + V <= n) {
+        body(std::integral_constant<int, V>(), e0);
+    } else {
+        for (int64_t e = e0; e < n; ++e) body(std::integral_constant<int, 1>(), e);
+    }
 }
 
 }  // namespace femq

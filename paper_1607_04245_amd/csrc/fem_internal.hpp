@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <initializer_list>
+
 #include "fem.h"
 
 namespace femq {
@@ -50,12 +52,26 @@ struct MeshArgs {
     int32_t* counts;  // optional
 };
 
+enum RowOrder { kOrderLaunch = 0, kOrderXcd = 1, kOrderRuns = 2 };
+constexpr int kRun = 16;
+
 struct Launch {
     int grid;      // workgroups
     int block;     // threads per workgroup (multiple of 64)
     int vec;       // elements per lane in load/store phases
     hipStream_t stream;
+    bool stream_out = true;  // output rows leave with streaming stores (row_st)
+    int order = 0;           // place of each workgroup, RowOrder (row_block)
 };
+
+// Whether rows of n words in each of the given arrays (NULL ones are skipped)
+// all start on a 128-byte cache line.
+inline bool whole_lines(int64_t n, size_t word, std::initializer_list<const void*> arrays) {
+    if ((size_t)n * word % 128 != 0) return false;
+    for (const void* p : arrays)
+        if (reinterpret_cast<uintptr_t>(p) % 128 != 0) return false;
+    return true;
+}
 
 // Each returns hipErrorInvalidValue when the combination has no kernel;
 // `space` is the coefficient space (fem_coef_space).
@@ -125,7 +141,7 @@ struct BatchMesh {              // device-side descriptor, one per mesh
 // d_tile_mesh may be NULL: each workgroup then finds its first mesh by a
 // binary search over the n_mesh descriptors' tile ranges.
 hipError_t launch_batch(int dtype, const BatchMesh* d_meshes, int n_mesh, const int32_t* d_tile_mesh,
-                        int64_t n_tiles, int tile_elems, const Launch& l);
+                        int64_t n_tiles, const Launch& l);
 
 // Threads the transpose kernel needs per workgroup for a given tuning, or 0 if
 // the combination is not supported by that strategy.

@@ -24,7 +24,7 @@ namespace femq {
 // than it needs. EPT = 1 is software-pipelined: the next tile's connectivity
 // is in flight while the current tile's vertices are gathered and processed.
 // EPT > 1 gives each lane EPT independent gather chains instead.
-template <int DIM, typename Out, int EPT, bool VEC>
+template <int DIM, typename Out, int EPT, bool VEC, bool STREAM_OUT>
 __global__ void __launch_bounds__(512)
 geometry_kernel(int64_t n, int64_t nv, const double* __restrict__ X, const int32_t* __restrict__ conn,
                 Out* __restrict__ inv_j, Out* __restrict__ det_j, int32_t* __restrict__ counts) {
@@ -50,7 +50,7 @@ geometry_kernel(int64_t n, int64_t nv, const double* __restrict__ X, const int32
                 __builtin_amdgcn_sched_barrier(0);
                 const int64_t next = tile + waves;
                 load_conn<DIM, VEC>(conn, clamp(next < t_end ? next * 64 + lane : n), vb);
-                geometry_finish<DIM, Out>(e < n, e, n, ok, x, inv_j, det_j, ndeg, npoor);
+                geometry_finish<DIM, STREAM_OUT, Out>(e < n, e, n, ok, x, inv_j, det_j, ndeg, npoor);
                 tile = next;
             }
             if (tile >= t_end) break;
@@ -63,7 +63,7 @@ geometry_kernel(int64_t n, int64_t nv, const double* __restrict__ X, const int32
                 __builtin_amdgcn_sched_barrier(0);
                 const int64_t next = tile + waves;
                 load_conn<DIM, VEC>(conn, clamp(next < t_end ? next * 64 + lane : n), va);
-                geometry_finish<DIM, Out>(e < n, e, n, ok, x, inv_j, det_j, ndeg, npoor);
+                geometry_finish<DIM, STREAM_OUT, Out>(e < n, e, n, ok, x, inv_j, det_j, ndeg, npoor);
                 tile = next;
             }
         }
@@ -81,7 +81,7 @@ geometry_kernel(int64_t n, int64_t nv, const double* __restrict__ X, const int32
             for (int j = 0; j < EPT; ++j) gather_coords<DIM>(X, v[j], nv, x[j]);
 #pragma unroll
             for (int j = 0; j < EPT; ++j)
-                geometry_finish<DIM, Out>(e[j] < n, e[j], n, (e[j] < n) & conn_ok<DIM>(v[j], nv), x[j], inv_j, det_j,
+                geometry_finish<DIM, STREAM_OUT, Out>(e[j] < n, e[j], n, (e[j] < n) & conn_ok<DIM>(v[j], nv), x[j], inv_j, det_j,
                                           ndeg, npoor);
         }
     }
@@ -91,21 +91,16 @@ geometry_kernel(int64_t n, int64_t nv, const double* __restrict__ X, const int32
 template <int DIM, typename Out, bool VEC>
 static hipError_t launch_e(int64_t n, int64_t nv, const double* X, const int32_t* conn, Out* ij, Out* dj,
                            int32_t* counts, const Launch& l) {
+    auto go = [&](auto ept_c) {
+        constexpr int EPT = decltype(ept_c)::value;
+        const auto k = l.stream_out ? geometry_kernel<DIM, Out, EPT, VEC, true> : geometry_kernel<DIM, Out, EPT, VEC, false>;
+        hipLaunchKernelGGL(k, dim3(l.grid), dim3(l.block), 0, l.stream, n, nv, X, conn, ij, dj, counts);
+    };
     switch (l.vec) {
-    case 1:
-        hipLaunchKernelGGL((geometry_kernel<DIM, Out, 1, VEC>), dim3(l.grid), dim3(l.block), 0, l.stream, n, nv, X,
-                           conn, ij, dj, counts);
-        break;
-    case 2:
-        hipLaunchKernelGGL((geometry_kernel<DIM, Out, 2, VEC>), dim3(l.grid), dim3(l.block), 0, l.stream, n, nv, X,
-                           conn, ij, dj, counts);
-        break;
-    case 4:
-        hipLaunchKernelGGL((geometry_kernel<DIM, Out, 4, VEC>), dim3(l.grid), dim3(l.block), 0, l.stream, n, nv, X,
-                           conn, ij, dj, counts);
-        break;
-    default:
-        return hipErrorInvalidValue;
+    case 1: go(std::integral_constant<int, 1>()); break;
+    case 2: go(std::integral_constant<int, 2>()); break;
+    case 4: go(std::integral_constant<int, 4>()); break;
+    default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }

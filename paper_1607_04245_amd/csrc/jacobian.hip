@@ -176,7 +176,7 @@ __device__ __forceinline__ void coef_moments(const Real* __restrict__ coef, int6
 }
 
 // Mass matrix K_bb' = sum_q k_q phi_b(x_q) phi_b'(x_q), stored directly.
-template <int DIM, int ORDER, int RULE, int SPACE, typename Real>
+template <int DIM, int ORDER, int RULE, int SPACE, bool STREAM_OUT, typename Real>
 __device__ __forceinline__ void mass_matrix(const Real* __restrict__ coef, int64_t n, int64_t e, Real dj,
                                             Real* __restrict__ out) {
     using Q = RuleBary<DIM, RULE>;
@@ -194,8 +194,8 @@ __device__ __forceinline__ void mass_matrix(const Real* __restrict__ coef, int64
                 auto lam = [q](int v) { return Q::lam(q, v); };
                 s = fmadd(Real(Bs::value(b, lam) * Bs::value(bp, lam)), k[0][q], s);
             }
-            __builtin_nontemporal_store(s, out + (int64_t)(b * NB + bp) * n + e);
-            if constexpr (bp != b) __builtin_nontemporal_store(s, out + (int64_t)(bp * NB + b) * n + e);
+            row_st<STREAM_OUT>(s, out + (int64_t)(b * NB + bp) * n + e);
+            if constexpr (bp != b) row_st<STREAM_OUT>(s, out + (int64_t)(bp * NB + b) * n + e);
         });
     });
 }
@@ -217,20 +217,20 @@ __device__ __forceinline__ void with_scheme(int rule, int space, const F& f) {
     else by_space(std::integral_constant<int, OTHER>());
 }
 
-template <int DIM, int PHYS, int ORDER, typename Real>
+template <int DIM, int PHYS, int ORDER, bool STREAM_OUT, typename Real>
 __global__ void __launch_bounds__(256)
-jacobian_kernel(int64_t n, int rule, int space, const Real* __restrict__ inv_j, const Real* __restrict__ det_j,
+jacobian_kernel(int64_t n, int order, int rule, int space, const Real* __restrict__ inv_j, const Real* __restrict__ det_j,
                 const Real* __restrict__ coef, Real* __restrict__ out) {
     using Bs = LagBasis<DIM, ORDER>;
     constexpr int NV = DIM + 1, NB = Bs::NB;
     constexpr int NC = PHYS == FEM_ELASTICITY ? DIM : 1, NBT = NB * NC;
     constexpr int NCOEF = PHYS == FEM_ELASTICITY ? 2 : 1;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += stride) {
+    for (int64_t e = row_block(order) * blockDim.x + threadIdx.x; e < n; e += stride) {
         const Real dj = fabs(__builtin_nontemporal_load(det_j + e));
         if constexpr (PHYS == FEM_MASS) {
             with_scheme<DIM, ORDER>(rule, space, [&](auto rule_c, auto space_c) {
-                mass_matrix<DIM, ORDER, decltype(rule_c)::value, decltype(space_c)::value, Real>(coef, n, e, dj, out);
+                mass_matrix<DIM, ORDER, decltype(rule_c)::value, decltype(space_c)::value, STREAM_OUT, Real>(coef, n, e, dj, out);
             });
         } else {
             Moments<NV, Real> M[NCOEF];
@@ -302,8 +302,8 @@ jacobian_kernel(int64_t n, int rule, int space, const Real* __restrict__ inv_j, 
                         for (int cp = 0; cp < NC; ++cp) {
                             if (bp == b && cp < c) continue;
                             const int r = b * NC + c, s = bp * NC + cp;
-                            __builtin_nontemporal_store(blk[c][cp], out + (int64_t)(r * NBT + s) * n + e);
-                            if (s != r) __builtin_nontemporal_store(blk[c][cp], out + (int64_t)(s * NBT + r) * n + e);
+                            row_st<STREAM_OUT>(blk[c][cp], out + (int64_t)(r * NBT + s) * n + e);
+                            if (s != r) row_st<STREAM_OUT>(blk[c][cp], out + (int64_t)(s * NBT + r) * n + e);
                         }
                 });
             });
@@ -313,8 +313,8 @@ jacobian_kernel(int64_t n, int rule, int space, const Real* __restrict__ inv_j, 
 
 template <int DIM, int PHYS, int ORDER, typename Real>
 static hipError_t launch_jac(int rule, int space, const JacobianArgs& a, const Launch& l) {
-    hipLaunchKernelGGL((jacobian_kernel<DIM, PHYS, ORDER, Real>), dim3(l.grid), dim3(l.block), 0, l.stream, a.n, rule,
-                       space, static_cast<const Real*>(a.inv_j), static_cast<const Real*>(a.det_j),
+    const auto k = l.stream_out ? jacobian_kernel<DIM, PHYS, ORDER, true, Real> : jacobian_kernel<DIM, PHYS, ORDER, false, Real>;
+    hipLaunchKernelGGL(k, dim3(l.grid), dim3(l.block), 0, l.stream, a.n, l.order, rule, space, static_cast<const Real*>(a.inv_j), static_cast<const Real*>(a.det_j),
                        static_cast<const Real*>(a.coef), static_cast<Real*>(a.out));
     return hipGetLastError();
 }

@@ -96,7 +96,7 @@ __device__ __forceinline__ bool mesh_stage_gather(MeshStage<Elem<DIM, PHYS, RULE
 // Geometry, integration and stores of one element whose vertices are in x.
 // The arithmetic runs for every lane; only the stores and the counters are
 // predicated on `valid`, so no load feeding it can be moved into a branch.
-template <int DIM, int PHYS, int RULE, typename Real, bool STORE_GEOM>
+template <int DIM, int PHYS, int RULE, typename Real, bool STORE_GEOM, bool STREAM_OUT>
 __device__ __forceinline__ void mesh_element_finish(bool valid, int64_t e, int64_t n, bool ok,
                                                     const double (&x)[DIM + 1][DIM], const Real* uu, const Real* cf,
                                                     Real* __restrict__ out, Real* __restrict__ inv_j,
@@ -117,11 +117,11 @@ __device__ __forceinline__ void mesh_element_finish(bool valid, int64_t e, int64
     if (valid) {
         if constexpr (STORE_GEOM) {
 #pragma unroll
-            for (int f = 0; f < E::NG; ++f) __builtin_nontemporal_store(ij[f], inv_j + f * n + e);
-            __builtin_nontemporal_store(dj, det_j + e);
+            for (int f = 0; f < E::NG; ++f) row_st<STREAM_OUT>(ij[f], inv_j + f * n + e);
+            row_st<STREAM_OUT>(dj, det_j + e);
         }
 #pragma unroll
-        for (int f = 0; f < E::NBT; ++f) __builtin_nontemporal_store(r[f], out + f * n + e);
+        for (int f = 0; f < E::NBT; ++f) row_st<STREAM_OUT>(r[f], out + f * n + e);
     }
 }
 
@@ -134,7 +134,7 @@ __device__ __forceinline__ void mesh_element_finish(bool valid, int64_t e, int64
 // pipelining.
 // GATHER: u (and a P1 coefficient) are vertex arrays gathered through the
 // connectivity instead of per-element closure rows.
-template <int DIM, int PHYS, int RULE, typename Real, int EPT, bool STORE_GEOM, bool VEC, bool GATHER>
+template <int DIM, int PHYS, int RULE, typename Real, int EPT, bool STORE_GEOM, bool VEC, bool GATHER, bool STREAM_OUT>
 __global__ void __launch_bounds__(512)
 residual_mesh_kernel(int64_t n, int64_t nv, const double* __restrict__ X, const int32_t* __restrict__ conn,
                      const Real* __restrict__ u, const Real* __restrict__ coef,
@@ -165,7 +165,7 @@ residual_mesh_kernel(int64_t n, int64_t nv, const double* __restrict__ X, const 
                 __builtin_amdgcn_sched_barrier(0);
                 const int64_t next = tile + waves;
                 mesh_stage_load<DIM, PHYS, RULE, Real, VEC, GATHER>(b, next < t_end ? next * 64 + lane : n, n, conn, u, coef);
-                mesh_element_finish<DIM, PHYS, RULE, Real, STORE_GEOM>(e < n, e, n, ok, x, a.u, a.cf, out, inv_j,
+                mesh_element_finish<DIM, PHYS, RULE, Real, STORE_GEOM, STREAM_OUT>(e < n, e, n, ok, x, a.u, a.cf, out, inv_j,
                                                                        det_j, ndeg, npoor);
                 tile = next;
             }
@@ -180,7 +180,7 @@ residual_mesh_kernel(int64_t n, int64_t nv, const double* __restrict__ X, const 
                 __builtin_amdgcn_sched_barrier(0);
                 const int64_t next = tile + waves;
                 mesh_stage_load<DIM, PHYS, RULE, Real, VEC, GATHER>(a, next < t_end ? next * 64 + lane : n, n, conn, u, coef);
-                mesh_element_finish<DIM, PHYS, RULE, Real, STORE_GEOM>(e < n, e, n, ok, x, b.u, b.cf, out, inv_j,
+                mesh_element_finish<DIM, PHYS, RULE, Real, STORE_GEOM, STREAM_OUT>(e < n, e, n, ok, x, b.u, b.cf, out, inv_j,
                                                                        det_j, ndeg, npoor);
                 tile = next;
             }
@@ -200,7 +200,7 @@ residual_mesh_kernel(int64_t n, int64_t nv, const double* __restrict__ X, const 
             for (int j = 0; j < EPT; ++j) ok[j] = mesh_stage_gather<DIM, PHYS, RULE, Real, GATHER>(st[j], e[j], n, nv, X, u, coef, x[j]);
 #pragma unroll
             for (int j = 0; j < EPT; ++j)
-                mesh_element_finish<DIM, PHYS, RULE, Real, STORE_GEOM>(e[j] < n, e[j], n, ok[j], x[j], st[j].u,
+                mesh_element_finish<DIM, PHYS, RULE, Real, STORE_GEOM, STREAM_OUT>(e[j] < n, e[j], n, ok[j], x[j], st[j].u,
                                                                        st[j].cf, out, inv_j, det_j, ndeg, npoor);
         }
     }
@@ -214,12 +214,16 @@ static hipError_t launch_s(const MeshArgs& a, const Launch& l) {
     Real* out = static_cast<Real*>(a.out);
     Real* ij = static_cast<Real*>(a.inv_j);
     Real* dj = static_cast<Real*>(a.det_j);
-    if (ij != nullptr)
-        hipLaunchKernelGGL((residual_mesh_kernel<DIM, PHYS, RULE, Real, EPT, true, VEC, GATHER>), dim3(l.grid), dim3(l.block),
-                           0, l.stream, a.n, a.n_vert, a.coords, a.conn, u, cf, out, ij, dj, a.counts);
-    else
-        hipLaunchKernelGGL((residual_mesh_kernel<DIM, PHYS, RULE, Real, EPT, false, VEC, GATHER>), dim3(l.grid), dim3(l.block),
-                           0, l.stream, a.n, a.n_vert, a.coords, a.conn, u, cf, out, ij, dj, a.counts);
+    auto go = [&](auto geom_c, auto whole_c) {
+        hipLaunchKernelGGL((residual_mesh_kernel<DIM, PHYS, RULE, Real, EPT, decltype(geom_c)::value, VEC, GATHER,
+                                                 decltype(whole_c)::value>),
+                           dim3(l.grid), dim3(l.block), 0, l.stream, a.n, a.n_vert, a.coords, a.conn, u, cf, out, ij, dj,
+                           a.counts);
+    };
+    const std::true_type yes;
+    const std::false_type no;
+    if (ij != nullptr) l.stream_out ? go(yes, yes) : go(yes, no);
+    else l.stream_out ? go(no, yes) : go(no, no);
     return hipGetLastError();
 }
 
@@ -227,9 +231,10 @@ static hipError_t launch_s(const MeshArgs& a, const Launch& l) {
 // needs 16-byte aligned connectivity; torch allocations always are.
 template <int DIM, int PHYS, int RULE, typename Real, int EPT, bool GATHER>
 static hipError_t launch_a(const MeshArgs& a, const Launch& l) {
-    const bool vec = DIM == 3 && (reinterpret_cast<uintptr_t>(a.conn) % 16) == 0;
-    return vec ? launch_s<DIM, PHYS, RULE, Real, EPT, true, GATHER>(a, l)
-               : launch_s<DIM, PHYS, RULE, Real, EPT, false, GATHER>(a, l);
+    if constexpr (DIM == 3) {
+        if (reinterpret_cast<uintptr_t>(a.conn) % 16 == 0) return launch_s<DIM, PHYS, RULE, Real, EPT, true, GATHER>(a, l);
+    }
+    return launch_s<DIM, PHYS, RULE, Real, EPT, false, GATHER>(a, l);
 }
 
 template <int DIM, int PHYS, int RULE, typename Real, bool GATHER>

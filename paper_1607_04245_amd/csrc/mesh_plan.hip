@@ -54,13 +54,13 @@ __device__ __forceinline__ void wave_sync() {
 // holds, per tile, maxc x DIM coordinates (FP64), then, after all tiles'
 // coordinates, maxc x (NU + NK) values of u and of a P1 coefficient (gather
 // form).
-template <int DIM, int PHYS, int RULE, typename Real, bool GATHER, bool STORE_GEOM, int TPW>
+template <int DIM, int PHYS, int RULE, typename Real, bool GATHER, bool STORE_GEOM, int TPW, bool STREAM_OUT>
 __global__ void __launch_bounds__(64)
 residual_planned_kernel(int64_t n, int64_t n_tiles, const int64_t* __restrict__ tile_off,
                         const int32_t* __restrict__ tile_verts, const uint32_t* __restrict__ lidx,
                         const double* __restrict__ X, const Real* __restrict__ u, const Real* __restrict__ coef,
                         Real* __restrict__ out, Real* __restrict__ inv_j, Real* __restrict__ det_j,
-                        int32_t* __restrict__ counts, int maxc) {
+                        int32_t* __restrict__ counts, int maxc, int order) {
     using E = Elem<DIM, PHYS, RULE>;
     constexpr bool CV = coef_per_vertex<DIM, PHYS, RULE, GATHER>();
     constexpr int NU = GATHER ? E::NC : 0, NK = CV ? E::NCOEF : 0, NR = NU + NK;
@@ -69,7 +69,7 @@ residual_planned_kernel(int64_t n, int64_t n_tiles, const int64_t* __restrict__ 
     Real* vs = reinterpret_cast<Real*>(plan_lds + (int64_t)TPW * maxc * DIM);
     const int lane = threadIdx.x;
     int ndeg = 0, npoor = 0;
-    for (int64_t t0 = (int64_t)blockIdx.x * TPW; t0 < n_tiles; t0 += (int64_t)gridDim.x * TPW) {
+    for (int64_t t0 = row_block(order) * TPW; t0 < n_tiles; t0 += (int64_t)gridDim.x * TPW) {
         int64_t off[TPW], e[TPW];
         int cnt[TPW];
         uint32_t li[TPW];
@@ -135,7 +135,7 @@ residual_planned_kernel(int64_t n, int64_t n_tiles, const int64_t* __restrict__ 
                     for (int m = 0; m < E::NCOEF; ++m) cf[k][m * E::NB + b] = vk[l * NR + NU + m];
                 }
             }
-            mesh_element_finish<DIM, PHYS, RULE, Real, STORE_GEOM>(e[k] < n, e[k], n, true, x, uu[k], cf[k], out,
+            mesh_element_finish<DIM, PHYS, RULE, Real, STORE_GEOM, STREAM_OUT>(e[k] < n, e[k], n, true, x, uu[k], cf[k], out,
                                                                    inv_j, det_j, ndeg, npoor);
         }
         wave_sync();  // every lane has read the tiles before the next ones are staged
@@ -145,16 +145,16 @@ residual_planned_kernel(int64_t n, int64_t n_tiles, const int64_t* __restrict__ 
 
 // The geometry alone through the plan: coordinates staged as above, then
 // the epilogue of fem_geometry, so the outputs are bitwise its outputs.
-template <int DIM, typename Out>
+template <int DIM, typename Out, bool STREAM_OUT>
 __global__ void __launch_bounds__(64)
 geometry_planned_kernel(int64_t n, int64_t n_tiles, const int64_t* __restrict__ tile_off,
                         const int32_t* __restrict__ tile_verts, const uint32_t* __restrict__ lidx,
                         const double* __restrict__ X, Out* __restrict__ inv_j, Out* __restrict__ det_j,
-                        int32_t* __restrict__ counts) {
+                        int32_t* __restrict__ counts, int order) {
     extern __shared__ double plan_lds[];
     const int lane = threadIdx.x;
     int ndeg = 0, npoor = 0;
-    for (int64_t t = blockIdx.x; t < n_tiles; t += gridDim.x) {
+    for (int64_t t = row_block(order); t < n_tiles; t += gridDim.x) {
         const int64_t off = tile_off[t];
         const int cnt = (int)(tile_off[t + 1] - off);
         const int64_t e = t * kPlanTile + lane, ec = e < n ? e : n - 1;
@@ -172,7 +172,7 @@ geometry_planned_kernel(int64_t n, int64_t n_tiles, const int64_t* __restrict__ 
 #pragma unroll
             for (int i = 0; i < DIM; ++i) x[b][i] = plan_lds[l * DIM + i];
         }
-        geometry_finish<DIM, Out>(e < n, e, n, true, x, inv_j, det_j, ndeg, npoor);
+        geometry_finish<DIM, STREAM_OUT, Out>(e < n, e, n, true, x, inv_j, det_j, ndeg, npoor);
         wave_sync();
     }
     add_counts(counts, ndeg, npoor);
@@ -202,17 +202,19 @@ static hipError_t launch_planned_t(const PlannedArgs& a) {
     const size_t lds = (size_t)TPW * maxc * (DIM * sizeof(double) + NR * sizeof(Real));
     const int64_t grid =
         std::min<int64_t>(std::max<int64_t>((a.p->n_tiles + TPW - 1) / TPW, 1), (int64_t)1 << 30);
-    if (a.inv_j != nullptr)
-        hipLaunchKernelGGL((residual_planned_kernel<DIM, PHYS, RULE, Real, GATHER, true, TPW>), dim3((unsigned)grid),
-                           dim3(64), lds, a.stream, a.p->n_elem, a.p->n_tiles, a.p->tile_off, a.p->tile_verts, a.p->lidx,
-                           a.coords, static_cast<const Real*>(a.u), static_cast<const Real*>(a.coef),
-                           static_cast<Real*>(a.out), static_cast<Real*>(a.inv_j), static_cast<Real*>(a.det_j),
-                           a.counts, maxc);
-    else
-        hipLaunchKernelGGL((residual_planned_kernel<DIM, PHYS, RULE, Real, GATHER, false, TPW>), dim3((unsigned)grid),
-                           dim3(64), lds, a.stream, a.p->n_elem, a.p->n_tiles, a.p->tile_off, a.p->tile_verts, a.p->lidx,
-                           a.coords, static_cast<const Real*>(a.u), static_cast<const Real*>(a.coef),
-                           static_cast<Real*>(a.out), nullptr, nullptr, a.counts, maxc);
+    const bool whole = whole_lines(a.p->n_elem, sizeof(Real), {a.out, a.inv_j, a.det_j});
+    auto go = [&](auto geom_c, auto whole_c) {
+        hipLaunchKernelGGL((residual_planned_kernel<DIM, PHYS, RULE, Real, GATHER, decltype(geom_c)::value, TPW,
+                                                    decltype(whole_c)::value>),
+                           dim3((unsigned)grid), dim3(64), lds, a.stream, a.p->n_elem, a.p->n_tiles, a.p->tile_off,
+                           a.p->tile_verts, a.p->lidx, a.coords, static_cast<const Real*>(a.u),
+                           static_cast<const Real*>(a.coef), static_cast<Real*>(a.out), static_cast<Real*>(a.inv_j),
+                           static_cast<Real*>(a.det_j), a.counts, maxc, whole ? kOrderLaunch : kOrderXcd);
+    };
+    const std::true_type yes;
+    const std::false_type no;
+    if (a.inv_j != nullptr) whole ? go(yes, yes) : go(yes, no);
+    else whole ? go(no, yes) : go(no, no);
     return hipGetLastError();
 }
 
@@ -390,9 +392,11 @@ fem_status fem_geometry_planned(const fem_mesh_plan* plan, const double* coords,
     auto go = [&](auto dim_c, auto out_c) {
         constexpr int D = decltype(dim_c)::value;
         using Out = typename decltype(out_c)::type;
-        hipLaunchKernelGGL((geometry_planned_kernel<D, Out>), dim3(grid), dim3(64), lds, s, plan->n_elem,
-                           plan->n_tiles, plan->tile_off, plan->tile_verts, plan->lidx, coords,
-                           static_cast<Out*>(inv_j), static_cast<Out*>(det_j), counts);
+        const bool whole = whole_lines(plan->n_elem, sizeof(Out), {inv_j, det_j});
+        const auto k = whole ? geometry_planned_kernel<D, Out, true> : geometry_planned_kernel<D, Out, false>;
+        hipLaunchKernelGGL(k, dim3(grid), dim3(64), lds, s, plan->n_elem, plan->n_tiles, plan->tile_off,
+                           plan->tile_verts, plan->lidx, coords, static_cast<Out*>(inv_j), static_cast<Out*>(det_j),
+                           counts, whole ? kOrderLaunch : kOrderXcd);
     };
     struct F32 { using type = float; };
     struct F64 { using type = double; };

@@ -162,7 +162,7 @@ residual_dedup_kernel(int64_t n, int64_t nv, const double* __restrict__ X, const
 #pragma unroll
         for (int k = 0; k <= DIM; ++k) v0[k] = cur.v[k];
         const bool ok = (e < n) & conn_ok<DIM>(v0, nv);
-        mesh_element_finish<DIM, PHYS, RULE, Real, STORE_GEOM>(e < n, e, n, ok, x, cur.u, cur.cf, out, inv_j, det_j,
+        mesh_element_finish<DIM, PHYS, RULE, Real, STORE_GEOM, true>(e < n, e, n, ok, x, cur.u, cur.cf, out, inv_j, det_j,
                                                                ndeg, npoor);
         tile = next;
     };

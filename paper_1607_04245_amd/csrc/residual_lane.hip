@@ -2,8 +2,12 @@
 //
 // Each lane owns V consecutive elements. Every structure-of-arrays row is
 // read with one V-wide vector load per lane, so a wavefront reads 64*V
-// consecutive words of a row at once (fully coalesced, 16-byte accesses for
-// V*sizeof(Real) = 16). The quadrature phase (pointwise f0/f1 at every
+// consecutive words of a row at once (fully coalesced). Rows may start on any
+// word: the rows of an odd element count do, and V = 4 (FP32) or 2 (FP64) is
+// there for them, since a wave then shares only the two lines at the ends of
+// its 1 KB with other waves (P1 3D Laplacian FP32, 1,500,001 tets: 31.5 us
+// with one element per lane and streaming stores, 23-26 us with four and
+// plain stores, floor 20.5 us). The quadrature phase (pointwise f0/f1 at every
 // point) and the basis phase (sum back onto the basis functions) run in
 // registers, so no value crosses lanes and no reduction is needed; the paper's
 // concern about per-thread storage (Section 1) does not bind on gfx950, whose
@@ -13,39 +17,25 @@
 
 namespace femq {
 
-template <int DIM, int PHYS, int RULE, typename Real, int V>
+template <int DIM, int PHYS, int RULE, typename Real, int V, bool STREAM_OUT>
 __global__ void __launch_bounds__(512)
-residual_lane_kernel(int64_t n, const Real* __restrict__ inv_j, const Real* __restrict__ det_j,
+residual_lane_kernel(int64_t n, int order, const Real* __restrict__ inv_j, const Real* __restrict__ det_j,
                      const Real* __restrict__ u, const Real* __restrict__ coef,
                      Real* __restrict__ out) {
     using E = Elem<DIM, PHYS, RULE>;
-    const int64_t nchunk = n / V;  // the host guarantees V divides n
+    const int64_t nchunk = (n + V - 1) / V;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t ch = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; ch < nchunk; ch += stride) {
-        const int64_t e0 = ch * V;
-        Real rij[E::NG][V], rdj[V], ru[E::NBT][V], rcf[E::NCQ][V], rr[E::NBT][V];
-#pragma unroll
-        for (int f = 0; f < E::NG; ++f) ld_row<Real, V>(inv_j + f * n + e0, rij[f]);
-        ld_row<Real, V>(det_j + e0, rdj);
-#pragma unroll
-        for (int f = 0; f < E::NBT; ++f) ld_row<Real, V>(u + f * n + e0, ru[f]);
-#pragma unroll
-        for (int f = 0; f < E::NCQ; ++f) ld_row<Real, V>(coef + f * n + e0, rcf[f]);
-#pragma unroll
-        for (int v = 0; v < V; ++v) {
-            Real ij[E::NG], uu[E::NBT], cf[E::NCQ], r[E::NBT];
-#pragma unroll
-            for (int f = 0; f < E::NG; ++f) ij[f] = rij[f][v];
-#pragma unroll
-            for (int f = 0; f < E::NBT; ++f) uu[f] = ru[f][v];
-#pragma unroll
-            for (int f = 0; f < E::NCQ; ++f) cf[f] = rcf[f][v];
-            element_residual<DIM, PHYS, RULE, Real>(ij, rdj[v], uu, cf, r);
-#pragma unroll
-            for (int f = 0; f < E::NBT; ++f) rr[f][v] = r[f];
-        }
-#pragma unroll
-        for (int f = 0; f < E::NBT; ++f) st_row<Real, V>(out + f * n + e0, rr[f]);
+    for (int64_t ch = row_block(order) * blockDim.x + threadIdx.x; ch < nchunk; ch += stride) {
+        for_chunk<V>(ch * V, n, [&](auto width, int64_t e) {
+            constexpr int W = decltype(width)::value;
+            Real rij[E::NG][W], rdj[1][W], ru[E::NBT][W], rcf[E::NCQ][W], rr[E::NBT][W];
+            load_rows_v<E::NG>(inv_j, n, e, rij);
+            load_rows_v<1>(det_j, n, e, rdj);
+            load_rows_v<E::NBT>(u, n, e, ru);
+            load_rows_v<E::NCQ>(coef, n, e, rcf);
+            lane_residual<DIM, PHYS, RULE, Real>(rij, rdj, ru, rcf, rr);
+            store_rows_v<E::NBT, STREAM_OUT>(out, n, e, rr);
+        });
     }
 }
 
@@ -56,21 +46,17 @@ static hipError_t launch_v(const ResidualArgs& a, const Launch& l) {
     const Real* u = static_cast<const Real*>(a.u);
     const Real* cf = static_cast<const Real*>(a.coef);
     Real* out = static_cast<Real*>(a.out);
+    auto go = [&](auto vec_c) {
+        constexpr int V = decltype(vec_c)::value;
+        const auto k = l.stream_out ? residual_lane_kernel<DIM, PHYS, RULE, Real, V, true>
+                               : residual_lane_kernel<DIM, PHYS, RULE, Real, V, false>;
+        hipLaunchKernelGGL(k, dim3(l.grid), dim3(l.block), 0, l.stream, a.n, l.order, ij, dj, u, cf, out);
+    };
     switch (l.vec) {
-    case 1:
-        hipLaunchKernelGGL((residual_lane_kernel<DIM, PHYS, RULE, Real, 1>), dim3(l.grid), dim3(l.block), 0,
-                           l.stream, a.n, ij, dj, u, cf, out);
-        break;
-    case 2:
-        hipLaunchKernelGGL((residual_lane_kernel<DIM, PHYS, RULE, Real, 2>), dim3(l.grid), dim3(l.block), 0,
-                           l.stream, a.n, ij, dj, u, cf, out);
-        break;
-    case 4:
-        hipLaunchKernelGGL((residual_lane_kernel<DIM, PHYS, RULE, Real, 4>), dim3(l.grid), dim3(l.block), 0,
-                           l.stream, a.n, ij, dj, u, cf, out);
-        break;
-    default:
-        return hipErrorInvalidValue;
+    case 1: go(std::integral_constant<int, 1>()); break;
+    case 2: go(std::integral_constant<int, 2>()); break;
+    case 4: go(std::integral_constant<int, 4>()); break;
+    default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }

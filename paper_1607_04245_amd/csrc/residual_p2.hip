@@ -13,74 +13,68 @@
 
 namespace femq {
 
-template <int DIM, int PHYS, int RULE, int SPACE, typename Real>
+template <int DIM, int PHYS, int RULE, int SPACE, typename Real, bool STREAM_OUT>
 __global__ void __launch_bounds__(256)
-residual_p2_kernel(int64_t n, const Real* __restrict__ inv_j, const Real* __restrict__ det_j,
+residual_p2_kernel(int64_t n, int order, const Real* __restrict__ inv_j, const Real* __restrict__ det_j,
                    const Real* __restrict__ u, const Real* __restrict__ coef, Real* __restrict__ out) {
     using E = ElemP2<DIM, PHYS, RULE, SPACE>;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += stride) {
+    for (int64_t e = row_block(order) * blockDim.x + threadIdx.x; e < n; e += stride) {
         Real ij[E::NG], uu[E::NBT], cf[E::NCQ], r[E::NBT];
-#pragma unroll
-        for (int f = 0; f < E::NG; ++f) ij[f] = __builtin_nontemporal_load(inv_j + f * n + e);
-        const Real dj = __builtin_nontemporal_load(det_j + e);
-#pragma unroll
-        for (int f = 0; f < E::NBT; ++f) uu[f] = __builtin_nontemporal_load(u + f * n + e);
-#pragma unroll
-        for (int f = 0; f < E::NCQ; ++f) cf[f] = __builtin_nontemporal_load(coef + f * n + e);
+        load_rows<E::NG>(inv_j, n, e, ij);
+        const Real dj = row_ld(det_j + e);
+        load_rows<E::NBT>(u, n, e, uu);
+        load_rows<E::NCQ>(coef, n, e, cf);
         element_residual_p2<DIM, PHYS, RULE, SPACE, Real>(ij, dj, uu, cf, r);
-#pragma unroll
-        for (int f = 0; f < E::NBT; ++f) __builtin_nontemporal_store(r[f], out + f * n + e);
+        store_rows<E::NBT, STREAM_OUT>(out, n, e, r);
     }
 }
 
 // du = R(w) (symmetric forms), dcoef from element_dcoef_p2; either may be
 // skipped (wave-uniform flags), and u is read only for dcoef.
-template <int DIM, int PHYS, int RULE, int SPACE, typename Real>
+template <int DIM, int PHYS, int RULE, int SPACE, typename Real, bool STREAM_OUT>
 __global__ void __launch_bounds__(256)
-backward_p2_kernel(int64_t n, const Real* __restrict__ inv_j, const Real* __restrict__ det_j,
+backward_p2_kernel(int64_t n, int order, const Real* __restrict__ inv_j, const Real* __restrict__ det_j,
                    const Real* __restrict__ u, const Real* __restrict__ coef, const Real* __restrict__ w,
                    Real* __restrict__ du, Real* __restrict__ dcoef) {
     using E = ElemP2<DIM, PHYS, RULE, SPACE>;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += stride) {
+    for (int64_t e = row_block(order) * blockDim.x + threadIdx.x; e < n; e += stride) {
         Real ij[E::NG], ww[E::NBT];
-#pragma unroll
-        for (int f = 0; f < E::NG; ++f) ij[f] = __builtin_nontemporal_load(inv_j + f * n + e);
-        const Real dj = __builtin_nontemporal_load(det_j + e);
-#pragma unroll
-        for (int f = 0; f < E::NBT; ++f) ww[f] = __builtin_nontemporal_load(w + f * n + e);
+        load_rows<E::NG>(inv_j, n, e, ij);
+        const Real dj = row_ld(det_j + e);
+        load_rows<E::NBT>(w, n, e, ww);
         if (du != nullptr) {
             Real cf[E::NCQ], r[E::NBT];
-#pragma unroll
-            for (int f = 0; f < E::NCQ; ++f) cf[f] = __builtin_nontemporal_load(coef + f * n + e);
+            load_rows<E::NCQ>(coef, n, e, cf);
             element_residual_p2<DIM, PHYS, RULE, SPACE, Real>(ij, dj, ww, cf, r);
-#pragma unroll
-            for (int f = 0; f < E::NBT; ++f) __builtin_nontemporal_store(r[f], du + f * n + e);
+            store_rows<E::NBT, STREAM_OUT>(du, n, e, r);
         }
         if (dcoef != nullptr) {
             Real uu[E::NBT], d[E::NCQ];
-#pragma unroll
-            for (int f = 0; f < E::NBT; ++f) uu[f] = __builtin_nontemporal_load(u + f * n + e);
+            load_rows<E::NBT>(u, n, e, uu);
             element_dcoef_p2<DIM, PHYS, RULE, SPACE, Real>(ij, dj, uu, ww, d);
-#pragma unroll
-            for (int f = 0; f < E::NCQ; ++f) __builtin_nontemporal_store(d[f], dcoef + f * n + e);
+            store_rows<E::NCQ, STREAM_OUT>(dcoef, n, e, d);
         }
     }
 }
 
 template <int DIM, int PHYS, int RULE, int SPACE, typename Real>
 static hipError_t launch_fwd(const ResidualArgs& a, const Launch& l) {
-    hipLaunchKernelGGL((residual_p2_kernel<DIM, PHYS, RULE, SPACE, Real>), dim3(l.grid), dim3(l.block), 0, l.stream,
-                       a.n, static_cast<const Real*>(a.inv_j), static_cast<const Real*>(a.det_j),
+    const auto k = l.stream_out ? residual_p2_kernel<DIM, PHYS, RULE, SPACE, Real, true>
+                           : residual_p2_kernel<DIM, PHYS, RULE, SPACE, Real, false>;
+    hipLaunchKernelGGL(k, dim3(l.grid), dim3(l.block), 0, l.stream,
+                       a.n, l.order, static_cast<const Real*>(a.inv_j), static_cast<const Real*>(a.det_j),
                        static_cast<const Real*>(a.u), static_cast<const Real*>(a.coef), static_cast<Real*>(a.out));
     return hipGetLastError();
 }
 
 template <int DIM, int PHYS, int RULE, int SPACE, typename Real>
 static hipError_t launch_bwd(const BackwardArgs& a, const Launch& l) {
-    hipLaunchKernelGGL((backward_p2_kernel<DIM, PHYS, RULE, SPACE, Real>), dim3(l.grid), dim3(l.block), 0, l.stream,
-                       a.n, static_cast<const Real*>(a.inv_j), static_cast<const Real*>(a.det_j),
+    const auto k = l.stream_out ? backward_p2_kernel<DIM, PHYS, RULE, SPACE, Real, true>
+                           : backward_p2_kernel<DIM, PHYS, RULE, SPACE, Real, false>;
+    hipLaunchKernelGGL(k, dim3(l.grid), dim3(l.block), 0, l.stream,
+                       a.n, l.order, static_cast<const Real*>(a.inv_j), static_cast<const Real*>(a.det_j),
                        static_cast<const Real*>(a.u), static_cast<const Real*>(a.coef), static_cast<const Real*>(a.w),
                        static_cast<Real*>(a.du), static_cast<Real*>(a.dcoef));
     return hipGetLastError();

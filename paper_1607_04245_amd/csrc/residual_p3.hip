@@ -13,24 +13,21 @@
 
 namespace femq {
 
-template <int DIM, int PHYS, typename Real>
+template <int DIM, int PHYS, typename Real, bool STREAM_OUT>
 __global__ void __launch_bounds__(256)
-residual_p3_kernel(int64_t n, int space, const Real* __restrict__ inv_j, const Real* __restrict__ det_j,
+residual_p3_kernel(int64_t n, int order, int space, const Real* __restrict__ inv_j, const Real* __restrict__ det_j,
                    const Real* __restrict__ u, const Real* __restrict__ coef, Real* __restrict__ out) {
     constexpr int RULE = DIM == 2 ? FEM_RULE_TRI6 : FEM_RULE_TET11;
     using E = ElemP3<DIM, PHYS, RULE, FEM_COEF_QUAD>;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += stride) {
+    for (int64_t e = row_block(order) * blockDim.x + threadIdx.x; e < n; e += stride) {
         Real ij[E::NG], uu[E::NBT], aq[E::NCQ], r[E::NBT];
-#pragma unroll
-        for (int f = 0; f < E::NG; ++f) ij[f] = __builtin_nontemporal_load(inv_j + f * n + e);
-        const Real dj = __builtin_nontemporal_load(det_j + e);
-#pragma unroll
-        for (int f = 0; f < E::NBT; ++f) uu[f] = __builtin_nontemporal_load(u + f * n + e);
+        load_rows<E::NG>(inv_j, n, e, ij);
+        const Real dj = row_ld(det_j + e);
+        load_rows<E::NBT>(u, n, e, uu);
         p3_coef_points<DIM, PHYS, RULE, Real>(space, coef, n, e, aq);
         element_residual_p3<DIM, PHYS, RULE, Real>(ij, dj, uu, aq, r);
-#pragma unroll
-        for (int f = 0; f < E::NBT; ++f) __builtin_nontemporal_store(r[f], out + f * n + e);
+        store_rows<E::NBT, STREAM_OUT>(out, n, e, r);
     }
 }
 
@@ -38,37 +35,32 @@ residual_p3_kernel(int64_t n, int space, const Real* __restrict__ inv_j, const R
 // to the coefficient words: the point values mapped back onto the space
 // (the transpose of p3_coef_points). Either output may be skipped
 // (uniform flags); u is read only for dcoef.
-template <int DIM, int PHYS, typename Real>
+template <int DIM, int PHYS, typename Real, bool STREAM_OUT>
 __global__ void __launch_bounds__(256)
-backward_p3_kernel(int64_t n, int space, const Real* __restrict__ inv_j, const Real* __restrict__ det_j,
+backward_p3_kernel(int64_t n, int order, int space, const Real* __restrict__ inv_j, const Real* __restrict__ det_j,
                    const Real* __restrict__ u, const Real* __restrict__ coef, const Real* __restrict__ w,
                    Real* __restrict__ du, Real* __restrict__ dcoef) {
     constexpr int RULE = DIM == 2 ? FEM_RULE_TRI6 : FEM_RULE_TET11;
     using E = ElemP3<DIM, PHYS, RULE, FEM_COEF_QUAD>;
     using Q = RuleP2<DIM, RULE>;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += stride) {
+    for (int64_t e = row_block(order) * blockDim.x + threadIdx.x; e < n; e += stride) {
         Real ij[E::NG], ww[E::NBT];
-#pragma unroll
-        for (int f = 0; f < E::NG; ++f) ij[f] = __builtin_nontemporal_load(inv_j + f * n + e);
-        const Real dj = __builtin_nontemporal_load(det_j + e);
-#pragma unroll
-        for (int f = 0; f < E::NBT; ++f) ww[f] = __builtin_nontemporal_load(w + f * n + e);
+        load_rows<E::NG>(inv_j, n, e, ij);
+        const Real dj = row_ld(det_j + e);
+        load_rows<E::NBT>(w, n, e, ww);
         if (du != nullptr) {
             Real aq[E::NCQ], r[E::NBT];
             p3_coef_points<DIM, PHYS, RULE, Real>(space, coef, n, e, aq);
             element_residual_p3<DIM, PHYS, RULE, Real>(ij, dj, ww, aq, r);
-#pragma unroll
-            for (int f = 0; f < E::NBT; ++f) __builtin_nontemporal_store(r[f], du + f * n + e);
+            store_rows<E::NBT, STREAM_OUT>(du, n, e, r);
         }
         if (dcoef != nullptr) {
             Real uu[E::NBT], dq[E::NCQ];
-#pragma unroll
-            for (int f = 0; f < E::NBT; ++f) uu[f] = __builtin_nontemporal_load(u + f * n + e);
+            load_rows<E::NBT>(u, n, e, uu);
             element_dcoef_points_p3<DIM, PHYS, RULE, Real>(ij, dj, uu, ww, dq);
             if (space == FEM_COEF_QUAD) {
-#pragma unroll
-                for (int f = 0; f < E::NCQ; ++f) __builtin_nontemporal_store(dq[f], dcoef + f * n + e);
+                store_rows<E::NCQ, STREAM_OUT>(dcoef, n, e, dq);
             } else if (space == FEM_COEF_P1) {
 #pragma unroll
                 for (int m = 0; m < E::NCOEF; ++m)
@@ -77,7 +69,7 @@ backward_p3_kernel(int64_t n, int space, const Real* __restrict__ inv_j, const R
                         Real t = Real(0);
 #pragma unroll
                         for (int q = 0; q < E::NQ; ++q) t = fmadd(Real(Q::lam(q, v)), dq[m * E::NQ + q], t);
-                        __builtin_nontemporal_store(t, dcoef + (m * E::NV + v) * n + e);
+                        row_st<STREAM_OUT>(t, dcoef + (m * E::NV + v) * n + e);
                     }
             } else {
 #pragma unroll
@@ -85,7 +77,7 @@ backward_p3_kernel(int64_t n, int space, const Real* __restrict__ inv_j, const R
                     Real t = Real(0);
 #pragma unroll
                     for (int q = 0; q < E::NQ; ++q) t += dq[m * E::NQ + q];
-                    __builtin_nontemporal_store(t, dcoef + m * n + e);
+                    row_st<STREAM_OUT>(t, dcoef + m * n + e);
                 }
             }
         }
@@ -109,9 +101,9 @@ __device__ __forceinline__ const auto& p3_table() {
     else return kP3Table3;
 }
 
-template <int DIM, int PHYS, typename Real>
+template <int DIM, int PHYS, typename Real, bool STREAM_OUT>
 __global__ void __launch_bounds__(256)
-jacobian_p3_kernel(int64_t n, int space, const Real* __restrict__ inv_j, const Real* __restrict__ det_j,
+jacobian_p3_kernel(int64_t n, int order, int space, const Real* __restrict__ inv_j, const Real* __restrict__ det_j,
                    const Real* __restrict__ coef, Real* __restrict__ out) {
     constexpr int RULE = DIM == 2 ? FEM_RULE_TRI6 : FEM_RULE_TET11;
     using E = ElemP3<DIM, PHYS, RULE, FEM_COEF_QUAD>;
@@ -121,11 +113,10 @@ jacobian_p3_kernel(int64_t n, int space, const Real* __restrict__ inv_j, const R
     constexpr int M = E::NBT, NC = E::NC, NV = E::NV, NB = E::NB;
     const auto& tab = p3_table<DIM>();
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += stride) {
+    for (int64_t e = row_block(order) * blockDim.x + threadIdx.x; e < n; e += stride) {
         Real ij[E::NG], aq[E::NCQ];
-#pragma unroll
-        for (int f = 0; f < E::NG; ++f) ij[f] = __builtin_nontemporal_load(inv_j + f * n + e);
-        const Real adj = fabs(__builtin_nontemporal_load(det_j + e));
+        load_rows<E::NG>(inv_j, n, e, ij);
+        const Real adj = fabs(row_ld(det_j + e));
         p3_coef_points<DIM, PHYS, RULE, Real>(space, coef, n, e, aq);
         Real g[NV][DIM];
         p2_bary_grads<DIM, Real>(ij, g);
@@ -197,8 +188,8 @@ jacobian_p3_kernel(int64_t n, int space, const Real* __restrict__ inv_j, const R
 #pragma unroll
             for (int f = 0; f < M; ++f) {
                 if (f <= s) {
-                    __builtin_nontemporal_store(r[f], out + (int64_t)(f * M + s) * n + e);
-                    __builtin_nontemporal_store(r[f], out + (int64_t)(s * M + f) * n + e);
+                    row_st<STREAM_OUT>(r[f], out + (int64_t)(f * M + s) * n + e);
+                    row_st<STREAM_OUT>(r[f], out + (int64_t)(s * M + f) * n + e);
                 }
             }
         }
@@ -207,7 +198,8 @@ jacobian_p3_kernel(int64_t n, int space, const Real* __restrict__ inv_j, const R
 
 template <int DIM, int PHYS, typename Real>
 static hipError_t launch_jac(int space, const JacobianArgs& a, const Launch& l) {
-    hipLaunchKernelGGL((jacobian_p3_kernel<DIM, PHYS, Real>), dim3(l.grid), dim3(l.block), 0, l.stream, a.n, space,
+    const auto k = l.stream_out ? jacobian_p3_kernel<DIM, PHYS, Real, true> : jacobian_p3_kernel<DIM, PHYS, Real, false>;
+    hipLaunchKernelGGL(k, dim3(l.grid), dim3(l.block), 0, l.stream, a.n, l.order, space,
                        static_cast<const Real*>(a.inv_j), static_cast<const Real*>(a.det_j),
                        static_cast<const Real*>(a.coef), static_cast<Real*>(a.out));
     return hipGetLastError();
@@ -215,7 +207,8 @@ static hipError_t launch_jac(int space, const JacobianArgs& a, const Launch& l) 
 
 template <int DIM, int PHYS, typename Real>
 static hipError_t launch_bwd(int space, const BackwardArgs& a, const Launch& l) {
-    hipLaunchKernelGGL((backward_p3_kernel<DIM, PHYS, Real>), dim3(l.grid), dim3(l.block), 0, l.stream, a.n, space,
+    const auto k = l.stream_out ? backward_p3_kernel<DIM, PHYS, Real, true> : backward_p3_kernel<DIM, PHYS, Real, false>;
+    hipLaunchKernelGGL(k, dim3(l.grid), dim3(l.block), 0, l.stream, a.n, l.order, space,
                        static_cast<const Real*>(a.inv_j), static_cast<const Real*>(a.det_j),
                        static_cast<const Real*>(a.u), static_cast<const Real*>(a.coef), static_cast<const Real*>(a.w),
                        static_cast<Real*>(a.du), static_cast<Real*>(a.dcoef));
@@ -224,7 +217,8 @@ static hipError_t launch_bwd(int space, const BackwardArgs& a, const Launch& l) 
 
 template <int DIM, int PHYS, typename Real>
 static hipError_t launch_fwd(int space, const ResidualArgs& a, const Launch& l) {
-    hipLaunchKernelGGL((residual_p3_kernel<DIM, PHYS, Real>), dim3(l.grid), dim3(l.block), 0, l.stream, a.n, space,
+    const auto k = l.stream_out ? residual_p3_kernel<DIM, PHYS, Real, true> : residual_p3_kernel<DIM, PHYS, Real, false>;
+    hipLaunchKernelGGL(k, dim3(l.grid), dim3(l.block), 0, l.stream, a.n, l.order, space,
                        static_cast<const Real*>(a.inv_j), static_cast<const Real*>(a.det_j),
                        static_cast<const Real*>(a.u), static_cast<const Real*>(a.coef), static_cast<Real*>(a.out));
     return hipGetLastError();

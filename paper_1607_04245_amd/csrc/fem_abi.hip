@@ -548,10 +548,6 @@ fem_status fem_integrate_residual_p3(int dim, int physics, int rule, int coef_sp
         const size_t word = dtype == FEM_F32 ? 4 : 8;
         set_rows(l, whole_lines(n_elem, word, {elem_vec}),
                  n_elem * (int64_t)word * row_words(dim, physics, rule, coef_space, 3, 2, 1));
-        if (whole_lines(n_elem, word, {elem_vec})) {
-            l.stream_out = true;
-            l.order = kOrderLaunch;
-        }
         e = launch_residual_p3(dim, physics, coef_space, dtype, a, l);
     }
     return e == hipSuccess ? FEM_OK : hip_fail(e, "fem_integrate_residual_p3 launch");
@@ -597,10 +593,6 @@ fem_status fem_integrate_residual_p3_backward(int dim, int physics, int rule, in
     const size_t word = dtype == FEM_F32 ? 4 : 8;
     set_rows(l, whole_lines(n_elem, word, {du, dcoef}),
              n_elem * (int64_t)word * row_words(dim, physics, rule, coef_space, 3, (du ? 2 : 1) + (dcoef ? 1 : 0), (du ? 1 : 0) + (dcoef ? 1 : 0)));
-    if (whole_lines(n_elem, word, {du, dcoef})) {
-        l.stream_out = true;
-        l.order = kOrderLaunch;
-    }
     hipError_t e = launch_backward_p3(dim, physics, coef_space, dtype, a, l);
     return e == hipSuccess ? FEM_OK : hip_fail(e, "fem_integrate_residual_p3_backward launch");
 }

@@ -111,6 +111,165 @@ __device__ __forceinline__ void unroll_for(const F& f) {
     }
 }
 
+// The P3 tetrahedron at the eleven-point rule. The points form three orbits
+// (centroid; a high coordinate at one vertex; at both vertices of an edge), and as a
+// function of the point du/dlam_v takes only a few shapes: its coefficients
+// depend on lam_v and, at one other vertex p, on whether lam_p differs from
+// the remaining two. So with the sums over the other vertices o
+//   A = sum_o u(node near v on edge vo),  B = sum_o u(node near o),
+//   F = sum of u over the faces at v,
+// five combinations of (u_v, A, B, F) serve all eleven points, six of them
+// after a correction of three terms in the words of vertex p alone: 53
+// operations per v and component, where the products of the tabulated
+// derivatives take 110. The basis phase is the transpose.
+struct P3Tet {
+    using Q = RuleP2<3, FEM_RULE_TET11>;
+    // node of edge (v, o) near v; face without vertex p
+    __host__ __device__ static constexpr int edge_node(int v, int o) {
+        return 4 + 2 * ElemP2<3, 0, 0, 0>::edge_of(v, o) + (v < o ? 0 : 1);
+    }
+    __host__ __device__ static constexpr int face_without(int p) { return 19 - p; }
+    // k-th vertex other than v, and the vertex left over beside v and p, p'
+    __host__ __device__ static constexpr int other(int v, int k) { return k < v ? k : k + 1; }
+    __host__ __device__ static constexpr int edge_point(int a, int b) { return 5 + ElemP2<3, 0, 0, 0>::edge_of(a, b); }
+    // the edge that joins the two vertices other than a and b
+    __host__ __device__ static constexpr int opposite_point(int a, int b) {
+        return 5 + (5 - ElemP2<3, 0, 0, 0>::edge_of(a, b));
+    }
+    // The combinations: 0 centroid; 1 v's own vertex point; 2 another vertex
+    // point (p high); 3 an edge point at v (p the other end); 4 an edge point
+    // away from v (p the other low vertex). Their coefficients of u_v, A, B, F
+    // (j = 0..3) are entries of the derivative table at v = 0, and the
+    // corrections in u(node near v on vp), u(node near p), u(face without p)
+    // the differences of two entries, so both forms share the table's
+    // roundings: relative to extended precision an FP64 residual of 3D elasticity
+    // is off by 3.0e-16 (3.5e-16 with the products of the table).
+    static constexpr int point(int k) { return k == 0 ? 0 : k == 1 ? 1 : k == 2 ? 2 : k == 3 ? edge_point(0, 1) : edge_point(2, 3); }
+    static constexpr double base(int k, int j) {
+        return P3Basis<3, FEM_RULE_TET11>::dl(point(k), j == 0 ? 0 : j == 1 ? edge_node(0, 2) : j == 2 ? edge_node(2, 0)
+                                                                                              : face_without(3), 0);
+    }
+    // of combinations 2..4, with p = 1
+    static constexpr double corr(int k, int j) {
+        return P3Basis<3, FEM_RULE_TET11>::dl(point(k), j == 0 ? edge_node(0, 1) : j == 1 ? edge_node(1, 0) : face_without(1), 0) -
+               base(k, j + 1);
+    }
+
+    // Physical gradient of one component at every point: u[b * NC] its words,
+    // ij the inverse Jacobian; sink(q constant, gradient).
+    template <int NC, typename Real, typename Sink>
+    __device__ static __forceinline__ void gradients(const Real* u, const Real* ij, const Sink& sink) {
+        Real bs[4][5];
+        unroll_for<0, 4>([&](auto v_c) {
+            constexpr int v = decltype(v_c)::value;
+            constexpr int o0 = other(v, 0), o1 = other(v, 1), o2 = other(v, 2);
+            const Real a = (u[edge_node(v, o0) * NC] + u[edge_node(v, o1) * NC]) + u[edge_node(v, o2) * NC];
+            const Real b = (u[edge_node(o0, v) * NC] + u[edge_node(o1, v) * NC]) + u[edge_node(o2, v) * NC];
+            const Real f = (u[face_without(o0) * NC] + u[face_without(o1) * NC]) + u[face_without(o2) * NC];
+            unroll_for<0, 5>([&](auto k_c) {
+                constexpr int k = decltype(k_c)::value;
+                constexpr double c0 = base(k, 0), c1 = base(k, 1), c2 = base(k, 2), c3 = base(k, 3);
+                bs[v][k] = fmadd(Real(c3), f, fmadd(Real(c2), b, fmadd(Real(c1), a, Real(c0) * u[v * NC])));
+            });
+        });
+        auto at = [&](auto v_c, auto p_c, auto k_c) {
+            constexpr int v = decltype(v_c)::value, p = decltype(p_c)::value, k = decltype(k_c)::value;
+            constexpr double c0 = corr(k, 0), c1 = corr(k, 1), c2 = corr(k, 2);
+            return fmadd(Real(c2), u[face_without(p) * NC],
+                         fmadd(Real(c1), u[edge_node(p, v) * NC], fmadd(Real(c0), u[edge_node(v, p) * NC], bs[v][k])));
+        };
+        auto emit = [&](auto q_c, const Real (&d)[4]) {
+            Real g[3];
+#pragma unroll
+            for (int i = 0; i < 3; ++i)
+                g[i] = fmadd(d[3], ij[6 + i], fmadd(d[2], ij[3 + i], fmadd(d[1], ij[i], d[0] * -((ij[i] + ij[3 + i]) + ij[6 + i]))));
+            sink(q_c, g);
+        };
+        unroll_for<0, 11>([&](auto q_c) {
+            constexpr int q = decltype(q_c)::value;
+            Real d[4];
+            unroll_for<0, 4>([&](auto v_c) {
+                constexpr int v = decltype(v_c)::value;
+                if constexpr (q == 0) {
+                    d[v] = bs[v][0];
+                } else if constexpr (q < 5) {
+                    constexpr int p = q - 1;
+                    if constexpr (p == v) d[v] = bs[v][1];
+                    else d[v] = at(v_c, std::integral_constant<int, p>(), std::integral_constant<int, 2>());
+                } else {
+                    constexpr int i = Q::edge_i(q - 5), j = Q::edge_j(q - 5);
+                    if constexpr (v == i || v == j) {
+                        d[v] = at(v_c, std::integral_constant<int, i + j - v>(), std::integral_constant<int, 3>());
+                    } else {
+                        d[v] = at(v_c, std::integral_constant<int, 6 - i - j - v>(), std::integral_constant<int, 4>());
+                    }
+                }
+            });
+            emit(q_c, d);
+        });
+    }
+
+    // The transpose: r[b] of one component from the weighted flux at every
+    // point, flux(q constant, i).
+    template <typename Real, typename Flux>
+    __device__ static __forceinline__ void scatter(const Real* ij, const Flux& flux, Real (&r)[20]) {
+        Real h[11][4];  // g_v . flux
+        unroll_for<0, 11>([&](auto q_c) {
+            constexpr int q = decltype(q_c)::value;
+            const Real f0 = flux(q_c, 0), f1 = flux(q_c, 1), f2 = flux(q_c, 2);
+#pragma unroll
+            for (int k = 0; k < 3; ++k) h[q][k + 1] = fmadd(ij[k * 3 + 2], f2, fmadd(ij[k * 3 + 1], f1, ij[k * 3] * f0));
+            h[q][0] = fmadd(-((ij[2] + ij[5]) + ij[8]), f2, fmadd(-((ij[1] + ij[4]) + ij[7]), f1, -((ij[0] + ij[3]) + ij[6]) * f0));
+        });
+        unroll_for<0, 4>([&](auto v_c) {
+            constexpr int v = decltype(v_c)::value;
+            constexpr int o0 = other(v, 0), o1 = other(v, 1), o2 = other(v, 2);
+            const Real e[5] = {h[0][v], h[1 + v][v], (h[1 + o0][v] + h[1 + o1][v]) + h[1 + o2][v],
+                               (h[edge_point(v, o0)][v] + h[edge_point(v, o1)][v]) + h[edge_point(v, o2)][v],
+                               (h[opposite_point(v, o0)][v] + h[opposite_point(v, o1)][v]) + h[opposite_point(v, o2)][v]};
+            Real t[4];
+            unroll_for<0, 4>([&](auto j_c) {
+                constexpr int j = decltype(j_c)::value;
+                constexpr double c0 = base(0, j), c1 = base(1, j), c2 = base(2, j), c3 = base(3, j), c4 = base(4, j);
+                t[j] = fmadd(Real(c4), e[4], fmadd(Real(c3), e[3], fmadd(Real(c2), e[2], fmadd(Real(c1), e[1], Real(c0) * e[0]))));
+            });
+            r[v] = t[0];
+            unroll_for<0, 3>([&](auto n_c) {
+                constexpr int p = other(v, decltype(n_c)::value);
+                const Real hp[3] = {h[1 + p][v], h[edge_point(v, p)][v], h[opposite_point(v, p)][v]};
+                unroll_for<0, 3>([&](auto j_c) {
+                    constexpr int j = decltype(j_c)::value;
+                    constexpr int b = j == 0 ? edge_node(v, p) : j == 1 ? edge_node(p, v) : face_without(p);
+                    // an edge node is met at both its vertices, a face at its three
+                    constexpr bool first = j < 2 ? v < p : v == (p == 0 ? 1 : 0);
+                    constexpr double c2 = corr(2, j), c3 = corr(3, j), c4 = corr(4, j);
+                    Real x = t[j + 1];
+                    if constexpr (!first) x += r[b];
+                    r[b] = fmadd(Real(c4), hp[2], fmadd(Real(c3), hp[1], fmadd(Real(c2), hp[0], x)));
+                });
+            });
+        });
+    }
+};
+
+// f1 of the forms with a gradient term at one point, in place, from
+// coefficients that already carry the weight.
+template <int PHYS, int NC, typename Real>
+__device__ __forceinline__ void p3_weighted_flux(Real (&g)[NC][3], const Real* a) {
+    if constexpr (PHYS == FEM_LAPLACE) {
+#pragma unroll
+        for (int i = 0; i < 3; ++i) g[0][i] *= a[0];
+    } else {
+        const Real lt = a[0] * ((g[0][0] + g[1][1]) + g[2][2]), m2 = a[1] + a[1];
+        const Real s01 = a[1] * (g[0][1] + g[1][0]), s02 = a[1] * (g[0][2] + g[2][0]), s12 = a[1] * (g[1][2] + g[2][1]);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) g[c][c] = fmadd(m2, g[c][c], lt);
+        g[0][1] = g[1][0] = s01;
+        g[0][2] = g[2][0] = s02;
+        g[1][2] = g[2][1] = s12;
+    }
+}
+
 // The coefficient words of element e turned into values at the points: the
 // space is a uniform run-time branch (one kernel per dimension, physics and
 // type), the arithmetic after it is the same for every space. STREAM: the

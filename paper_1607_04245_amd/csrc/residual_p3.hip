@@ -6,12 +6,67 @@
 // rows) is one coalesced access per wave, and the quadrature and basis
 // phases run in registers with the basis tabulated at compile time
 // (p3_device.hpp). Workgroups hold at most four waves, so the largest
-// elements (3D elasticity in FP64, 60 closure and 60 output words) may use
-// the accumulation registers too instead of spilling to memory.
+// elements (3D elasticity in FP64) may use the accumulation registers too
+// instead of spilling to memory.
+//
+// Tetrahedra with a gradient term go through their point orbits (P3Tet): 3D
+// elasticity takes about 2300 vector instructions and 153 registers in FP32,
+// 307 in FP64, where the tabulated products took 4000, 178 and 395; so three
+// waves fit a SIMD in FP32. FP32, 600,032 tets, 365 MB: 92 -> 64 us (floor 57);
+// FP64, 2^20 tets, 1.28 GB: 284 -> 234 us (floor 198), one wave per SIMD. Their
+// adjoint holds the gradient of w once for both outputs and takes u component
+// by component (173 registers, and 348 with 40 of them spilled to the
+// accumulation registers; 209, and 512 with spills to memory before): 137 ->
+// 108 us and 311 -> 222 us at 600,032 tets (floors 109 and 219).
 #include "fem_internal.hpp"
 #include "p3_device.hpp"
 
 namespace femq {
+
+// Whether the element is evaluated through its point orbits (P3Tet): the
+// tetrahedron's forms with a gradient term. In phases: the gradient of every
+// component at all eleven points (99 words for elasticity, where the closure's
+// 60 die component by component), the flux in place of the gradient, and the
+// sums onto the basis, stored component by component.
+template <int DIM, int PHYS>
+constexpr bool p3_tet() { return DIM == 3 && Physics<PHYS>::HAS_F1; }
+
+// Gradient of every component at every point from the closure u[b * NC + c].
+template <int NC, typename Real>
+__device__ __forceinline__ void tet_gradients(const Real* u, const Real* ij, Real (&G)[11][NC][3]) {
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+        P3Tet::gradients<NC, Real>(u + c, ij, [&](auto q_c, const Real (&g)[3]) {
+#pragma unroll
+            for (int i = 0; i < 3; ++i) G[decltype(q_c)::value][c][i] = g[i];
+        });
+}
+
+// Weighted flux at every point in place of the gradient.
+template <int PHYS, int NC, typename Real>
+__device__ __forceinline__ void tet_flux(Real adj, const Real* aq, Real (&G)[11][NC][3]) {
+    constexpr int NCOEF = PHYS == FEM_ELASTICITY ? 2 : 1;
+#pragma unroll
+    for (int q = 0; q < 11; ++q) {
+        Real a[NCOEF];
+#pragma unroll
+        for (int m = 0; m < NCOEF; ++m) a[m] = (Real(P3Tet::Q::w(q)) * adj) * aq[m * 11 + q];
+        p3_weighted_flux<PHYS, NC, Real>(G[q], a);
+    }
+}
+
+// The sums onto the basis, to the output rows of element e.
+template <int NC, bool STREAM_OUT, typename Real>
+__device__ __forceinline__ void tet_store(const Real* ij, const Real (&G)[11][NC][3], Real* __restrict__ out, int64_t n,
+                                          int64_t e) {
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+        Real r[20];
+        P3Tet::scatter<Real>(ij, [&](auto q_c, int i) { return G[decltype(q_c)::value][c][i]; }, r);
+#pragma unroll
+        for (int b = 0; b < 20; ++b) row_st<STREAM_OUT>(r[b], out + (b * NC + c) * n + e);
+    }
+}
 
 template <int DIM, int PHYS, typename Real, bool STREAM_OUT>
 __global__ void __launch_bounds__(256)
@@ -19,15 +74,25 @@ residual_p3_kernel(int64_t n, int order, int space, const Real* __restrict__ inv
                    const Real* __restrict__ u, const Real* __restrict__ coef, Real* __restrict__ out) {
     constexpr int RULE = DIM == 2 ? FEM_RULE_TRI6 : FEM_RULE_TET11;
     using E = ElemP3<DIM, PHYS, RULE, FEM_COEF_QUAD>;
+    using Q = RuleP2<DIM, RULE>;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t e = row_block(order) * blockDim.x + threadIdx.x; e < n; e += stride) {
-        Real ij[E::NG], uu[E::NBT], aq[E::NCQ], r[E::NBT];
+        Real ij[E::NG], uu[E::NBT], aq[E::NCQ];
         load_rows<E::NG>(inv_j, n, e, ij);
         const Real dj = row_ld(det_j + e);
         load_rows<E::NBT>(u, n, e, uu);
-        p3_coef_points<DIM, PHYS, RULE, Real>(space, coef, n, e, aq);
-        element_residual_p3<DIM, PHYS, RULE, Real>(ij, dj, uu, aq, r);
-        store_rows<E::NBT, STREAM_OUT>(out, n, e, r);
+        if constexpr (p3_tet<DIM, PHYS>()) {
+            Real G[E::NQ][E::NC][3];
+            tet_gradients<E::NC, Real>(uu, ij, G);
+            p3_coef_points<DIM, PHYS, RULE, Real>(space, coef, n, e, aq);
+            tet_flux<PHYS, E::NC, Real>(fabs(dj), aq, G);
+            tet_store<E::NC, STREAM_OUT, Real>(ij, G, out, n, e);
+        } else {
+            Real r[E::NBT];
+            p3_coef_points<DIM, PHYS, RULE, Real>(space, coef, n, e, aq);
+            element_residual_p3<DIM, PHYS, RULE, Real>(ij, dj, uu, aq, r);
+            store_rows<E::NBT, STREAM_OUT>(out, n, e, r);
+        }
     }
 }
 
@@ -49,16 +114,63 @@ backward_p3_kernel(int64_t n, int order, int space, const Real* __restrict__ inv
         load_rows<E::NG>(inv_j, n, e, ij);
         const Real dj = row_ld(det_j + e);
         load_rows<E::NBT>(w, n, e, ww);
-        if (du != nullptr) {
-            Real aq[E::NCQ], r[E::NBT];
-            p3_coef_points<DIM, PHYS, RULE, Real>(space, coef, n, e, aq);
-            element_residual_p3<DIM, PHYS, RULE, Real>(ij, dj, ww, aq, r);
-            store_rows<E::NBT, STREAM_OUT>(du, n, e, r);
+        Real dq[E::NCQ];
+        if constexpr (p3_tet<DIM, PHYS>()) {
+            Real G[E::NQ][E::NC][3];  // gradients of w
+            tet_gradients<E::NC, Real>(ww, ij, G);
+            const Real adj = fabs(dj);
+            if (dcoef != nullptr) {
+                // component c of u against row c of f1(w; e_m): the trace of
+                // grad u accumulates, and grad u : (grad w + grad w^T)
+#pragma unroll
+                for (int f = 0; f < E::NCQ; ++f) dq[f] = Real(0);
+#pragma unroll
+                for (int c = 0; c < E::NC; ++c) {
+                    Real uu[E::NB];
+#pragma unroll
+                    for (int b = 0; b < E::NB; ++b) uu[b] = row_ld(u + (b * E::NC + c) * n + e);
+                    P3Tet::gradients<1, Real>(uu, ij, [&](auto q_c, const Real (&g)[3]) {
+                        constexpr int q = decltype(q_c)::value;
+                        if constexpr (PHYS == FEM_LAPLACE) {
+                            dq[q] = fmadd(g[2], G[q][0][2], fmadd(g[1], G[q][0][1], g[0] * G[q][0][0]));
+                        } else {
+                            dq[q] += g[c];
+#pragma unroll
+                            for (int i = 0; i < 3; ++i) dq[E::NQ + q] = fmadd(g[i], G[q][c][i] + G[q][i][c], dq[E::NQ + q]);
+                        }
+                    });
+                }
+#pragma unroll
+                for (int q = 0; q < E::NQ; ++q) {
+                    const Real s = Real(Q::w(q)) * adj;
+                    if constexpr (PHYS == FEM_LAPLACE) {
+                        dq[q] *= s;
+                    } else {
+                        dq[q] *= s * ((G[q][0][0] + G[q][1][1]) + G[q][2][2]);
+                        dq[E::NQ + q] *= s;
+                    }
+                }
+            }
+            if (du != nullptr) {
+                Real aq[E::NCQ];
+                p3_coef_points<DIM, PHYS, RULE, Real>(space, coef, n, e, aq);
+                tet_flux<PHYS, E::NC, Real>(adj, aq, G);
+                tet_store<E::NC, STREAM_OUT, Real>(ij, G, du, n, e);
+            }
+        } else {
+            if (du != nullptr) {
+                Real aq[E::NCQ], r[E::NBT];
+                p3_coef_points<DIM, PHYS, RULE, Real>(space, coef, n, e, aq);
+                element_residual_p3<DIM, PHYS, RULE, Real>(ij, dj, ww, aq, r);
+                store_rows<E::NBT, STREAM_OUT>(du, n, e, r);
+            }
+            if (dcoef != nullptr) {
+                Real uu[E::NBT];
+                load_rows<E::NBT>(u, n, e, uu);
+                element_dcoef_points_p3<DIM, PHYS, RULE, Real>(ij, dj, uu, ww, dq);
+            }
         }
         if (dcoef != nullptr) {
-            Real uu[E::NBT], dq[E::NCQ];
-            load_rows<E::NBT>(u, n, e, uu);
-            element_dcoef_points_p3<DIM, PHYS, RULE, Real>(ij, dj, uu, ww, dq);
             if (space == FEM_COEF_QUAD) {
                 store_rows<E::NCQ, STREAM_OUT>(dcoef, n, e, dq);
             } else if (space == FEM_COEF_P1) {

@@ -313,8 +313,8 @@ fem_status fem_integrate_residual_p2_backward(int dim, int physics, int rule, in
  * instead of once per element that uses it, and otherwise compute exactly
  * what fem_integrate_residual_mesh / fem_integrate_residual_gather compute:
  * the element vectors are bitwise equal to theirs.
- *   conn [n_elem][dim+1] int32 device array; it is copied to the host once
- *   (the plan is built there and uploaded) and not referenced afterwards.
+ *   conn [n_elem][dim+1] int32 device array; the plan is built from it on the
+ *   device and does not reference it afterwards.
  * Every vertex index must lie in [0, n_vert) (else FEM_ERR_INVALID_ARG). The
  * plan holds about 4 + 4 N_tile_vertices / 64 bytes per element of device
  * memory and is bound to the device current at creation. Synchronizes

@@ -226,3 +226,41 @@ def test_full_size_meshes(cfg):
     wl = mg.config(cfg)
     for dt in DTYPES:
         check_against_mesh(wl, wl.conn, dt, mg.COEF_QUAD)
+
+
+def _tile_lists(conn):
+    """Distinct vertices of every 64-element tile, by numpy."""
+    return [np.unique(conn[t:t + 64]) for t in range(0, conn.shape[0], 64)]
+
+
+# one element, tile edges, more tiles than one step of the offset scan takes
+# (4096 tiles), and lists from one vertex to 64 (dim + 1) of them
+@pytest.mark.parametrize("dim", [2, 3])
+@pytest.mark.parametrize("n,n_vert,spread", [(1, 5, None), (63, 40, 40), (64, 1, 1), (65, 10**6, 10**6), (1000, 300, 7),
+                                             (4097, 10**6, 10**6), (262144 + 65, 5000, 900)])
+def test_plan_lists(dim, n, n_vert, spread):
+    rng = np.random.default_rng(n)
+    conn = rng.integers(0, min(spread or n_vert, n_vert), size=(n, dim + 1)).astype(np.int32)
+    conn[-1, 0] = n_vert - 1
+    plan = api.MeshPlan(torch.from_numpy(conn).cuda(), n_vert)
+    lists = _tile_lists(conn)
+    info = plan.info()
+    assert info["max_tile_vertices"] == max(len(x) for x in lists)
+    assert info["tile_vertices"] == sum(len(x) for x in lists)
+    assert (info["dim"], info["n_elem"], info["n_vert"]) == (dim, n, n_vert)
+    # every element reads its own vertices: the gathered geometry is fem_geometry's
+    coords = torch.from_numpy(rng.uniform(-1, 1, (n_vert, dim))).cuda()
+    dc = torch.from_numpy(conn).cuda()
+    got, want = plan.geometry(coords, torch.float64), api.fem_geometry(coords, dc, torch.float64)
+    for a, b in zip(got, want):
+        assert torch.equal(a.nan_to_num(nan=7.0), b.nan_to_num(nan=7.0))
+    plan.close()
+
+
+@pytest.mark.parametrize("value", [-1, -2**31, 50, 2**31 - 1])
+def test_plan_counts_bad_indices(value):
+    conn = torch.zeros((200, 4), dtype=torch.int32)
+    conn[:, 1:] = torch.tensor([1, 2, 3], dtype=torch.int32)
+    conn[7, 2] = conn[7, 3] = conn[199, 0] = value
+    with pytest.raises(N.FemError, match="3 vertex indices outside"):
+        api.MeshPlan(conn.cuda(), 50)

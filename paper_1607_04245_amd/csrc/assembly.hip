@@ -10,15 +10,20 @@
 // result is deterministic (no atomics) and is exactly the element-by-element
 // sum in increasing element order, evaluated in the working precision.
 //
-// The plan is built on the device: a count of slots per vertex with integer
-// atomics (which also finds indices outside [0, n_vert)), an exclusive scan
-// for the row offsets, and a stable radix sort of the slot numbers keyed by
-// vertex, which leaves every row in increasing slot, hence element, order.
-// The rows are then stored sliced: for each group of 64 consecutive vertices
-// (one wave), slot j of all 64 rows is contiguous, and every row of the group
-// is padded with an empty marker to the group's longest row. A wave's j-th
-// slot load is then one contiguous 256-byte access instead of 64 accesses
-// one row apart; each vertex still sees its own slots in element order.
+// The rows are stored sliced: for each group of 64 consecutive vertices (one
+// wave), slot j of all 64 rows is contiguous, and every row of the group is
+// padded with an empty marker to the group's longest row. A wave's j-th slot
+// load is then one contiguous 256-byte access instead of 64 accesses one row
+// apart; each vertex sees its own slots in element order.
+//
+// The plan is built on the device. Integer atomics count the slots of every
+// vertex, find indices outside [0, n_vert) and hand every slot a place in its
+// row; the places depend on timing, so after the slots are stored a wave per
+// group sorts its 64 rows: it holds them in LDS and each entry counts the
+// smaller ones of its row. For 400,003 tets creating the plan takes 171 us
+// (377 us with a radix sort of all slots and its scratch). Meshes with a
+// vertex of more than kLdsRow elements take that sort (keyed by vertex, stable,
+// so rows stay in element order): its cost does not grow with the row.
 //
 // The restriction (closure) kernel is the adjoint: one lane per element
 // copies the vertex values of its d+1 vertices into the SoA closure rows.
@@ -36,6 +41,7 @@ struct fem_assembly_plan {
     int64_t n_elem = 0;
     int64_t n_vert = 0;
     int64_t n_groups = 0;          // ceil(n_vert / 64)
+    void* block = nullptr;         // the allocation that holds grp_off and grp_width
     int64_t* grp_off = nullptr;    // [n_groups + 1], first entry of each group in `sell`
     int32_t* grp_width = nullptr;  // [n_groups], slots per row in the group (its longest row)
     uint32_t* sell = nullptr;      // [grp_off[n_groups]]: group g, slot j, lane l at grp_off[g] + 64 j + l;
@@ -46,17 +52,25 @@ namespace femq {
 
 constexpr uint32_t kNoSlot = 0xFFFFFFFFu;
 
-// Slots per vertex, bad indices, and the identity slot numbering.
+// Rows up to this length are sorted in LDS: 64 rows of 256 slots fill 64 KB.
+constexpr int kLdsRow = 256;
+
+struct AssemblyTotals {
+    int64_t entries;   // of sell
+    int32_t widest;    // longest row
+    int32_t bad;       // indices outside [0, n_vert)
+};
+
+// Slots per vertex, each slot's place in its row, and bad indices.
 __global__ void __launch_bounds__(256)
 assembly_count_kernel(int64_t m, int64_t n_vert, const int32_t* __restrict__ conn, int32_t* __restrict__ count,
-                      uint32_t* __restrict__ ids, int32_t* __restrict__ bad) {
+                      uint32_t* __restrict__ place, int32_t* __restrict__ bad) {
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     int nbad = 0;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m; i += stride) {
         const int32_t v = conn[i];
-        ids[i] = (uint32_t)i;
         if (v >= 0 && (int64_t)v < n_vert)
-            atomicAdd(count + v, 1);
+            place[i] = (uint32_t)atomicAdd(count + v, 1);
         else
             ++nbad;
     }
@@ -64,21 +78,130 @@ assembly_count_kernel(int64_t m, int64_t n_vert, const int32_t* __restrict__ con
 }
 
 // Group widths: the longest row among each group's 64 vertices (vertices
-// past n_vert count as empty rows), and the padded size of the group.
+// past n_vert count as empty rows). One wave per group.
 __global__ void __launch_bounds__(256)
-assembly_width_kernel(int64_t n_groups, int64_t n_vert, const int32_t* __restrict__ row_ptr,
-                      int32_t* __restrict__ width, int64_t* __restrict__ size) {
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; g < n_groups; g += stride) {
-        const int64_t v0 = g * 64, v1 = v0 + 64 < n_vert ? v0 + 64 : n_vert;
-        int32_t w = 0;
-        for (int64_t v = v0; v < v1; ++v) w = max(w, row_ptr[v + 1] - row_ptr[v]);
-        width[g] = w;
-        size[g] = (int64_t)w * 64;
+assembly_width_kernel(int64_t n_groups, int64_t n_vert, const int32_t* __restrict__ count, int32_t* __restrict__ width) {
+    const int lane = threadIdx.x & 63;
+    const int64_t waves = (int64_t)gridDim.x * (blockDim.x >> 6);
+    for (int64_t g = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6); g < n_groups; g += waves) {
+        const int64_t v = g * 64 + lane;
+        int32_t w = v < n_vert ? count[v] : 0;
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) w = max(w, __shfl_xor(w, off, 64));
+        if (lane == 0) width[g] = w;
     }
 }
 
-// Sliced storage: entry (g, j, l) = slot j of vertex 64 g + l, or kNoSlot.
+// First entry of every group (off[n_groups] = all entries) and the longest
+// row. One workgroup walks the groups: 64 vertices each, so its 4096 widths
+// per step are 2^18 vertices.
+__global__ void __launch_bounds__(1024)
+assembly_scan_kernel(int64_t n_groups, const int32_t* __restrict__ width, int64_t* __restrict__ off,
+                     AssemblyTotals* __restrict__ totals) {
+    __shared__ int64_t wave_sum[16];
+    __shared__ int32_t wave_max[16];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    int64_t run = 0;
+    int32_t most = 0;
+    for (int64_t g0 = 0; g0 < n_groups; g0 += 4096) {
+        const int64_t g = g0 + 4 * (int64_t)threadIdx.x;
+        int64_t c[4], own = 0;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int32_t w = g + r < n_groups ? width[g + r] : 0;
+            most = max(most, w);
+            c[r] = (int64_t)w * 64;
+            own += c[r];
+        }
+        int64_t scan = own;   // inclusive over the wave
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int64_t x = __shfl_up(scan, o, 64);
+            if (lane >= o) scan += x;
+        }
+        if (lane == 63) wave_sum[wave] = scan;
+        __syncthreads();
+        int64_t at = run + scan - own;
+#pragma unroll
+        for (int w = 0; w < 16; ++w) {
+            if (w < wave) at += wave_sum[w];
+            run += wave_sum[w];
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            if (g + r < n_groups) off[g + r] = at;
+            at += c[r];
+        }
+        __syncthreads();   // wave_sum is read before the next step writes it
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) most = max(most, __shfl_xor(most, o, 64));
+    if (lane == 0) wave_max[wave] = most;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < 16; ++w) most = max(most, wave_max[w]);
+        off[n_groups] = run;
+        totals->entries = run;
+        totals->widest = most;
+    }
+}
+
+// Every slot to its place in its vertex's row.
+__global__ void __launch_bounds__(256)
+assembly_fill_kernel(int64_t m, const int32_t* __restrict__ conn, const uint32_t* __restrict__ place,
+                     const int64_t* __restrict__ off, uint32_t* __restrict__ sell) {
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m; i += stride) {
+        const int32_t v = conn[i];
+        sell[off[v / 64] + (int64_t)place[i] * 64 + v % 64] = (uint32_t)i;
+    }
+}
+
+// Sorts the rows of a group and pads them: one wave per group, its rows in
+// LDS (slot j of lane l at 64 j + l). An entry's place is the number of smaller
+// ones in its row.
+__global__ void __launch_bounds__(64)
+assembly_sort_kernel(int64_t n_groups, int64_t n_vert, const int32_t* __restrict__ count,
+                     const int32_t* __restrict__ width, const int64_t* __restrict__ off, uint32_t* __restrict__ sell) {
+    extern __shared__ uint32_t rows[];
+    const int lane = threadIdx.x;
+    for (int64_t g = blockIdx.x; g < n_groups; g += gridDim.x) {
+        const int64_t v = g * 64 + lane;
+        const int32_t w = width[g], len = v < n_vert ? count[v] : 0;
+        uint32_t* dst = sell + off[g] + lane;
+        for (int32_t j = 0; j < w; ++j) {
+            rows[j * 64 + lane] = j < len ? dst[(int64_t)j * 64] : kNoSlot;
+        }
+        __syncthreads();
+        // four entries at a time share the walk over the row
+        for (int32_t j = 0; j < w; j += 4) {
+            uint32_t x[4];
+            int32_t rank[4] = {0, 0, 0, 0};
+#pragma unroll
+            for (int r = 0; r < 4; ++r) x[r] = j + r < w ? rows[(j + r) * 64 + lane] : kNoSlot;
+#pragma unroll 4
+            for (int32_t i = 0; i < w; ++i) {
+                const uint32_t y = rows[i * 64 + lane];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) rank[r] += (int32_t)(y < x[r]);
+            }
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                if (j + r < len) dst[(int64_t)rank[r] * 64] = x[r];
+        }
+        for (int32_t j = len; j < w; ++j) dst[(int64_t)j * 64] = kNoSlot;
+        __syncthreads();   // the rows are read before the next group's are loaded
+    }
+}
+
+// The radix path: slot numbers to sort, and the sliced storage of its result,
+// entry (g, j, l) = slot j of vertex 64 g + l, or kNoSlot.
+__global__ void __launch_bounds__(256)
+assembly_ids_kernel(int64_t m, uint32_t* __restrict__ ids) {
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m; i += stride) ids[i] = (uint32_t)i;
+}
+
 __global__ void __launch_bounds__(256)
 assembly_slice_kernel(int64_t n_groups, int64_t n_vert, const int32_t* __restrict__ row_ptr,
                       const uint32_t* __restrict__ slots, const int32_t* __restrict__ width,
@@ -200,10 +323,47 @@ static hipError_t launch_restrict_nc(int nc, int64_t n_elem, int64_t n_vert, con
     return hipGetLastError();
 }
 
+// Fills p->sell from a stable radix sort of the slot numbers keyed by vertex:
+// the rows come out in slot, hence element, order at any length. `ids` is
+// scratch for the slot numbers, count[n_vert] is zero.
+static hipError_t slice_by_radix_sort(const fem_assembly_plan* p, const int32_t* conn, int64_t m, const int32_t* count,
+                                      uint32_t* ids, hipStream_t s) {
+    const int64_t nv = p->n_vert, ng = p->n_groups;
+    const uint32_t* keys = reinterpret_cast<const uint32_t*>(conn);  // valid indices are non-negative
+    int end_bit = 1;
+    while (end_bit < 32 && ((int64_t)1 << end_bit) < nv) ++end_bit;
+    int32_t* row_ptr = nullptr;
+    uint32_t *keys_out = nullptr, *slots = nullptr;
+    void* temp = nullptr;
+    size_t scan_bytes = 0, sort_bytes = 0;
+    hipError_t e = hipMalloc(&row_ptr, (size_t)(nv + 1) * sizeof(int32_t));
+    if (e == hipSuccess) e = hipMalloc(&keys_out, (size_t)m * sizeof(uint32_t));
+    if (e == hipSuccess) e = hipMalloc(&slots, (size_t)m * sizeof(uint32_t));
+    if (e == hipSuccess) e = hipcub::DeviceScan::ExclusiveSum(nullptr, scan_bytes, count, row_ptr, (int)(nv + 1), s);
+    if (e == hipSuccess)
+        e = hipcub::DeviceRadixSort::SortPairs(nullptr, sort_bytes, keys, keys_out, ids, slots, (int)m, 0, end_bit, s);
+    if (e == hipSuccess) e = hipMalloc(&temp, std::max(scan_bytes, sort_bytes) + 16);
+    if (e == hipSuccess) {
+        hipLaunchKernelGGL(assembly_ids_kernel, dim3(grid_for(m)), dim3(256), 0, s, m, ids);
+        e = hipGetLastError();
+    }
+    if (e == hipSuccess) e = hipcub::DeviceScan::ExclusiveSum(temp, scan_bytes, count, row_ptr, (int)(nv + 1), s);
+    if (e == hipSuccess)
+        e = hipcub::DeviceRadixSort::SortPairs(temp, sort_bytes, keys, keys_out, ids, slots, (int)m, 0, end_bit, s);
+    if (e == hipSuccess) {
+        hipLaunchKernelGGL(assembly_slice_kernel, dim3(grid_for(ng * 64)), dim3(256), 0, s, ng, nv, row_ptr, slots,
+                           p->grp_width, p->grp_off, p->sell);
+        e = hipGetLastError();
+    }
+    if (e == hipSuccess) e = hipStreamSynchronize(s);   // the scratch dies here
+    for (void* q : {(void*)row_ptr, (void*)keys_out, (void*)slots, temp})
+        if (q) (void)hipFree(q);
+    return e;
+}
+
 static void plan_free(fem_assembly_plan* p) {
     if (!p) return;
-    if (p->grp_off) (void)hipFree(p->grp_off);
-    if (p->grp_width) (void)hipFree(p->grp_width);
+    if (p->block) (void)hipFree(p->block);
     if (p->sell) (void)hipFree(p->sell);
     delete p;
 }
@@ -237,86 +397,57 @@ fem_status fem_assembly_plan_create(int dim, int64_t n_elem, int64_t n_vert, con
     p->n_vert = n_vert;
     p->n_groups = (n_vert + 63) / 64;
     const int64_t ng = p->n_groups;
+    // offsets, totals and widths share one allocation
+    const size_t off_bytes = (size_t)(ng + 1) * sizeof(int64_t);
     hipError_t e = hipGetDevice(&p->device);
-    if (e == hipSuccess) e = hipMalloc(&p->grp_off, (size_t)(ng + 1) * sizeof(int64_t));
-    if (e == hipSuccess && ng > 0) e = hipMalloc(&p->grp_width, (size_t)ng * sizeof(int32_t));
+    if (e == hipSuccess) e = hipMalloc(&p->block, off_bytes + sizeof(AssemblyTotals) + (size_t)ng * sizeof(int32_t));
     if (e != hipSuccess) { plan_free(p); return hip_fail(e, "fem_assembly_plan_create: hipMalloc"); }
+    p->grp_off = static_cast<int64_t*>(p->block);
+    AssemblyTotals* totals = reinterpret_cast<AssemblyTotals*>(static_cast<char*>(p->block) + off_bytes);
+    p->grp_width = reinterpret_cast<int32_t*>(totals + 1);
     if (m == 0) {  // no slots: every group has width 0
-        e = hipMemsetAsync(p->grp_off, 0, (size_t)(ng + 1) * sizeof(int64_t), s);
-        if (e == hipSuccess && ng > 0) e = hipMemsetAsync(p->grp_width, 0, (size_t)ng * sizeof(int32_t), s);
+        e = hipMemsetAsync(p->block, 0, off_bytes + sizeof(AssemblyTotals) + (size_t)ng * sizeof(int32_t), s);
         if (e == hipSuccess) e = hipStreamSynchronize(s);
         if (e != hipSuccess) { plan_free(p); return hip_fail(e, "fem_assembly_plan_create"); }
         *out = p;
         return FEM_OK;
     }
 
-    // scratch: counts (+ bad counter), compressed rows, identity slots, sorted
-    // keys and slots, group sizes, cub temp
+    // scratch: slots per vertex, and every slot's place in its row
     int32_t* count = nullptr;
-    int32_t* row_ptr = nullptr;
-    uint32_t* ids = nullptr;
-    uint32_t* keys_out = nullptr;
-    uint32_t* slots = nullptr;
-    int64_t* gsize = nullptr;
-    void* temp = nullptr;
-    size_t scan_bytes = 0, sort_bytes = 0, gscan_bytes = 0;
-    int end_bit = 1;
-    while (end_bit < 32 && ((int64_t)1 << end_bit) < n_vert) ++end_bit;
-    const uint32_t* keys_in = reinterpret_cast<const uint32_t*>(conn);  // valid indices are non-negative
-    auto cleanup = [&]() {
-        for (void* q : {(void*)count, (void*)row_ptr, (void*)ids, (void*)keys_out, (void*)slots, (void*)gsize, temp})
-            if (q) (void)hipFree(q);
-    };
-    e = hipMalloc(&count, (size_t)(n_vert + 2) * sizeof(int32_t));
-    if (e == hipSuccess) e = hipMalloc(&row_ptr, (size_t)(n_vert + 1) * sizeof(int32_t));
-    if (e == hipSuccess) e = hipMalloc(&ids, (size_t)m * sizeof(uint32_t));
-    if (e == hipSuccess) e = hipMalloc(&keys_out, (size_t)m * sizeof(uint32_t));
-    if (e == hipSuccess) e = hipMalloc(&slots, (size_t)m * sizeof(uint32_t));
-    if (e == hipSuccess) e = hipMalloc(&gsize, (size_t)(ng + 1) * sizeof(int64_t));
-    if (e == hipSuccess) e = hipcub::DeviceScan::ExclusiveSum(nullptr, scan_bytes, count, row_ptr, (int)(n_vert + 1), s);
-    if (e == hipSuccess)
-        e = hipcub::DeviceRadixSort::SortPairs(nullptr, sort_bytes, keys_in, keys_out, ids, slots, (int)m, 0, end_bit, s);
-    if (e == hipSuccess) e = hipcub::DeviceScan::ExclusiveSum(nullptr, gscan_bytes, gsize, p->grp_off, (int)(ng + 1), s);
-    if (e == hipSuccess) e = hipMalloc(&temp, std::max(std::max(scan_bytes, sort_bytes), gscan_bytes) + 16);
-    if (e == hipSuccess) e = hipMemsetAsync(count, 0, (size_t)(n_vert + 2) * sizeof(int32_t), s);
+    e = hipMalloc(&count, (size_t)(n_vert + 1) * sizeof(int32_t) + (size_t)m * sizeof(uint32_t));
+    if (e != hipSuccess) { plan_free(p); return hip_fail(e, "fem_assembly_plan_create: hipMalloc"); }
+    uint32_t* place = reinterpret_cast<uint32_t*>(count + n_vert + 1);
+    AssemblyTotals h{};
+    e = hipMemsetAsync(count, 0, (size_t)(n_vert + 1) * sizeof(int32_t), s);
+    if (e == hipSuccess) e = hipMemsetAsync(totals, 0, sizeof *totals, s);
     if (e == hipSuccess) {
-        hipLaunchKernelGGL(assembly_count_kernel, dim3(grid_for(m)), dim3(256), 0, s, m, n_vert, conn, count, ids,
-                           count + n_vert + 1);
+        hipLaunchKernelGGL(assembly_count_kernel, dim3(grid_for(m)), dim3(256), 0, s, m, n_vert, conn, count, place,
+                           &totals->bad);
+        hipLaunchKernelGGL(assembly_width_kernel, dim3(grid_for(ng * 64)), dim3(256), 0, s, ng, n_vert, count, p->grp_width);
+        hipLaunchKernelGGL(assembly_scan_kernel, dim3(1), dim3(1024), 0, s, ng, p->grp_width, p->grp_off, totals);
         e = hipGetLastError();
     }
-    int32_t bad = 0;
-    if (e == hipSuccess) e = hipMemcpyAsync(&bad, count + n_vert + 1, sizeof(int32_t), hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess) e = hipMemcpyAsync(&h, totals, sizeof h, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
-    if (e != hipSuccess) { cleanup(); plan_free(p); return hip_fail(e, "fem_assembly_plan_create: count"); }
-    if (bad) {
-        cleanup();
+    if (e == hipSuccess && h.bad) {
+        (void)hipFree(count);
         plan_free(p);
-        set_error("fem_assembly_plan_create: %d vertex indices outside [0, %lld)", bad, (long long)n_vert);
+        set_error("fem_assembly_plan_create: %d vertex indices outside [0, %lld)", (int)h.bad, (long long)n_vert);
         return FEM_ERR_INVALID_ARG;
     }
-    // count[n_vert] is zero, so row_ptr[n_vert] = m
-    e = hipcub::DeviceScan::ExclusiveSum(temp, scan_bytes, count, row_ptr, (int)(n_vert + 1), s);
-    if (e == hipSuccess)
-        e = hipcub::DeviceRadixSort::SortPairs(temp, sort_bytes, keys_in, keys_out, ids, slots, (int)m, 0, end_bit, s);
-    // group widths and offsets (gsize[ng] = 0, so grp_off[ng] is the total)
-    if (e == hipSuccess) e = hipMemsetAsync(gsize + ng, 0, sizeof(int64_t), s);
-    if (e == hipSuccess) {
-        hipLaunchKernelGGL(assembly_width_kernel, dim3(grid_for(ng)), dim3(256), 0, s, ng, n_vert, row_ptr,
-                           p->grp_width, gsize);
-        e = hipGetLastError();
-    }
-    if (e == hipSuccess) e = hipcub::DeviceScan::ExclusiveSum(temp, gscan_bytes, gsize, p->grp_off, (int)(ng + 1), s);
-    int64_t total = 0;
-    if (e == hipSuccess) e = hipMemcpyAsync(&total, p->grp_off + ng, sizeof(int64_t), hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
-    if (e == hipSuccess) e = hipMalloc(&p->sell, (size_t)std::max<int64_t>(total, 1) * sizeof(uint32_t));
-    if (e == hipSuccess) {
-        hipLaunchKernelGGL(assembly_slice_kernel, dim3(grid_for(ng * 64)), dim3(256), 0, s, ng, n_vert, row_ptr, slots,
+    if (e == hipSuccess) e = hipMalloc(&p->sell, (size_t)std::max<int64_t>(h.entries, 1) * sizeof(uint32_t));
+    if (e == hipSuccess && h.widest <= kLdsRow) {
+        hipLaunchKernelGGL(assembly_fill_kernel, dim3(grid_for(m)), dim3(256), 0, s, m, conn, place, p->grp_off, p->sell);
+        const int64_t grid = std::min<int64_t>(ng, (int64_t)1 << 22);
+        hipLaunchKernelGGL(assembly_sort_kernel, dim3((unsigned)grid), dim3(64), (size_t)h.widest * 256, s, ng, n_vert, count,
                            p->grp_width, p->grp_off, p->sell);
         e = hipGetLastError();
+    } else if (e == hipSuccess) {
+        e = slice_by_radix_sort(p, conn, m, count, place, s);
     }
     if (e == hipSuccess) e = hipStreamSynchronize(s);
-    cleanup();
+    (void)hipFree(count);
     if (e != hipSuccess) { plan_free(p); return hip_fail(e, "fem_assembly_plan_create: index build"); }
     *out = p;
     return FEM_OK;

@@ -201,3 +201,21 @@ def test_full_size_assembly(cfg):
     ref32 = oracle.assemble(wl.dim, nc, wl.n_vert, wl.conn, R32)
     scale = oracle.assemble(wl.dim, nc, wl.n_vert, wl.conn, np.abs(R32))
     assert (np.abs(F32 - ref32) / np.maximum(scale, 1e-300)).max() <= TOL[torch.float32]
+
+
+# the longest row on both sides of the length that is sorted in LDS (256
+# slots), no multiple of 64 vertices, and more vertex groups than one step of
+# the offset scan takes (4096 of 64 vertices)
+@pytest.mark.parametrize("dim", [2, 3])
+@pytest.mark.parametrize("n_elem,n_vert,star", [(1, 4, 1), (300, 129, 255), (300, 129, 256), (300, 129, 257), (5000, 70, 4000),
+                                                (40000, 4096 * 64 + 65, 200)])
+def test_assembly_rows_in_element_order(dim, n_elem, n_vert, star):
+    rng = np.random.default_rng(n_elem + star)
+    conn = rng.integers(1, n_vert, size=(n_elem, dim + 1)).astype(np.int32)
+    conn[rng.permutation(n_elem)[:star], rng.integers(0, dim + 1)] = 0   # vertex 0 lies in `star` elements
+    conn[-1, -1] = n_vert - 1
+    R = rng.normal(size=((dim + 1) * 2, n_elem))
+    plan = api.AssemblyPlan(dev(conn, torch.int32), n_vert)
+    F = plan.assemble(dev(R, torch.float64), 2).cpu().numpy()
+    assert np.array_equal(F, oracle.assemble(dim, 2, n_vert, conn, R))
+    plan.close()

@@ -219,3 +219,18 @@ def test_assembly_rows_in_element_order(dim, n_elem, n_vert, star):
     F = plan.assemble(dev(R, torch.float64), 2).cpu().numpy()
     assert np.array_equal(F, oracle.assemble(dim, 2, n_vert, conn, R))
     plan.close()
+
+
+@pytest.mark.parametrize("dtype", DTYPES)
+@pytest.mark.parametrize("dim,nc", [(2, 2), (3, 2), (3, 3)])
+# a wave per component below 2048 groups of 64 vertices, a wave per group from there on
+@pytest.mark.parametrize("n_vert", [2047 * 64, 2047 * 64 + 1])
+def test_assembly_component_split(dim, nc, dtype, n_vert):
+    rng = np.random.default_rng(n_vert)
+    n_elem = 60000
+    conn = rng.integers(0, n_vert, size=(n_elem, dim + 1)).astype(np.int32)
+    R = rng.integers(-8, 9, size=((dim + 1) * nc, n_elem)).astype(np.float64)   # exact sums in both types
+    plan = api.AssemblyPlan(dev(conn, torch.int32), n_vert)
+    F = plan.assemble(dev(R, dtype), nc).cpu().numpy()
+    assert np.array_equal(F, oracle.assemble(dim, nc, n_vert, conn, R))
+    plan.close()

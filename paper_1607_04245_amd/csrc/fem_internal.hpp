@@ -64,6 +64,19 @@ struct Launch {
     int order = 0;           // place of each workgroup, RowOrder (row_block)
 };
 
+// Workgroups that share a tile's element matrices, dealing out their `rows`
+// (columns, basis functions): as many as bring the launch to `want` waves, two
+// per SIMD. A wave writes its whole matrix in turn, so a small mesh waits for
+// one wave: P3 matrices of 2926 tets, 3D elasticity FP32 452 us with 46 waves, 21
+// with 44 workgroups per tile; P3 mass FP64 31 and 6; P2 3D elasticity FP32 44
+// and 35. With 4096 waves wanted, most of the larger ones lose what the inputs
+// read again cost (P2 3D elasticity FP32, 40,007 tets 69 and 101 us).
+inline int matrix_parts(const Launch& l, int rows, int64_t want = 2048) {
+    const int64_t waves = (int64_t)l.grid * (l.block / 64);
+    const int64_t parts = want / (waves < 1 ? 1 : waves);
+    return parts < 1 ? 1 : parts > rows ? rows : (int)parts;
+}
+
 // Whether rows of n words in each of the given arrays (NULL ones are skipped)
 // all start on a 128-byte cache line.
 inline bool whole_lines(int64_t n, size_t word, std::initializer_list<const void*> arrays) {

@@ -22,7 +22,8 @@
 // a short combination of moments and the products g_v . g_w of the physical
 // barycentric gradients. The mass term (products of basis values) is summed
 // over the points directly. The matrix is written exactly symmetric: each
-// entry below the diagonal is a copy of its mirror.
+// entry below the diagonal is a copy of its mirror. On small meshes blockIdx.y
+// deals the basis functions out to several workgroups per tile (matrix_parts).
 #include "fem_internal.hpp"
 #include "p2_device.hpp"
 
@@ -186,6 +187,7 @@ __device__ __forceinline__ void mass_matrix(const Real* __restrict__ coef, int64
     weighted_coef<DIM, RULE, SPACE, 1, Real>(coef, n, e, dj, k);
     static_for<0, NB>([&](auto b_c) {
         constexpr int b = decltype(b_c)::value;
+        if (b % gridDim.y != blockIdx.y) return;
         static_for<b, NB>([&](auto bp_c) {
             constexpr int bp = decltype(bp_c)::value;
             Real s = Real(0);
@@ -267,6 +269,7 @@ jacobian_kernel(int64_t n, int order, int rule, int space, const Real* __restric
                 }
             static_for<0, NB>([&](auto b_c) {
                 constexpr int b = decltype(b_c)::value;
+                if (b % gridDim.y != blockIdx.y) return;
                 static_for<b, NB>([&](auto bp_c) {
                     constexpr int bp = decltype(bp_c)::value;
                     Real blk[NC][NC];
@@ -314,7 +317,7 @@ jacobian_kernel(int64_t n, int order, int rule, int space, const Real* __restric
 template <int DIM, int PHYS, int ORDER, typename Real>
 static hipError_t launch_jac(int rule, int space, const JacobianArgs& a, const Launch& l) {
     const auto k = l.stream_out ? jacobian_kernel<DIM, PHYS, ORDER, true, Real> : jacobian_kernel<DIM, PHYS, ORDER, false, Real>;
-    hipLaunchKernelGGL(k, dim3(l.grid), dim3(l.block), 0, l.stream, a.n, l.order, rule, space, static_cast<const Real*>(a.inv_j), static_cast<const Real*>(a.det_j),
+    hipLaunchKernelGGL(k, dim3(l.grid, matrix_parts(l, LagBasis<DIM, ORDER>::NB)), dim3(l.block), 0, l.stream, a.n, l.order, rule, space, static_cast<const Real*>(a.inv_j), static_cast<const Real*>(a.det_j),
                        static_cast<const Real*>(a.coef), static_cast<Real*>(a.out));
     return hipGetLastError();
 }

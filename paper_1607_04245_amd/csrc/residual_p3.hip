@@ -203,7 +203,8 @@ backward_p3_kernel(int64_t n, int order, int space, const Real* __restrict__ inv
 // with the wave-uniform index b_s; the basis phase is the residual's, over
 // the rows r <= s only. Column s stores those entries at (r, s) and (s, r),
 // so the matrix is exactly symmetric. Columns run in a loop (the arithmetic
-// is inlined once).
+// is inlined once); blockIdx.y deals them out where the elements alone leave
+// the chip idle (matrix_parts).
 __constant__ P3Table<2, FEM_RULE_TRI6> kP3Table2;
 __constant__ P3Table<3, FEM_RULE_TET11> kP3Table3;
 
@@ -233,7 +234,7 @@ jacobian_p3_kernel(int64_t n, int order, int space, const Real* __restrict__ inv
         Real g[NV][DIM];
         p2_bary_grads<DIM, Real>(ij, g);
 #pragma unroll 1
-        for (int s = 0; s < M; ++s) {
+        for (int s = blockIdx.y; s < M; s += gridDim.y) {
             const int bs = s / NC, cs = s - bs * NC;
             Real r[M];
 #pragma unroll
@@ -310,8 +311,12 @@ jacobian_p3_kernel(int64_t n, int order, int space, const Real* __restrict__ inv
 
 template <int DIM, int PHYS, typename Real>
 static hipError_t launch_jac(int space, const JacobianArgs& a, const Launch& l) {
+    constexpr int M = ElemP3<DIM, PHYS, DIM == 2 ? FEM_RULE_TRI6 : FEM_RULE_TET11, FEM_COEF_QUAD>::NBT;
     const auto k = l.stream_out ? jacobian_p3_kernel<DIM, PHYS, Real, true> : jacobian_p3_kernel<DIM, PHYS, Real, false>;
-    hipLaunchKernelGGL(k, dim3(l.grid), dim3(l.block), 0, l.stream, a.n, l.order, space,
+    // the FP32 Laplacian is bound by its arithmetic and holds four waves per SIMD
+    // (100,003 tets: 67 us with 2048 waves wanted, 53 with 4096); the others hold two
+    const int64_t want = PHYS == FEM_LAPLACE && std::is_same<Real, float>::value ? 4096 : 2048;
+    hipLaunchKernelGGL(k, dim3(l.grid, matrix_parts(l, M, want)), dim3(l.block), 0, l.stream, a.n, l.order, space,
                        static_cast<const Real*>(a.inv_j), static_cast<const Real*>(a.det_j),
                        static_cast<const Real*>(a.coef), static_cast<Real*>(a.out));
     return hipGetLastError();

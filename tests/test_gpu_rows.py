@@ -165,3 +165,17 @@ def test_batch_widths(dtype, sizes):
             assert (m["buf"][:m["pad"]] == SENTINEL).all()
             assert (m["buf"][m["pad"] + r.numel():] == SENTINEL).all()
     plan.close()
+
+
+# small meshes share a tile's matrices among workgroups: one per column or basis
+# function (few tiles), some (8192 waves' worth of elements and below), none
+@pytest.mark.parametrize("dtype", DTYPES)
+@pytest.mark.parametrize("dim,physics,order", [(3, mg.LAPLACE, 1), (2, mg.MASS, 2), (3, mg.LAPLACE, 3), (2, mg.ELASTICITY, 3)])
+@pytest.mark.parametrize("n", [1, 300, 20000, 70001, 262145])
+def test_matrix_parts(dim, physics, order, dtype, n):
+    ij, dj, _, _, coef = _inputs(dim, physics, RULES[dim, order], order, n, dtype)
+    got = api.fem_integrate_jacobian(dim, physics, RULES[dim, order], ij, dj, coef, order=order)
+    for lo, hi in ((0, min(n, 64)), (max(0, n - 100), n)):
+        part = [t[..., lo:hi].contiguous() for t in (ij, dj, coef)]
+        ref = api.fem_integrate_jacobian(dim, physics, RULES[dim, order], *part, order=order)
+        assert torch.equal(got[..., lo:hi], ref)

@@ -152,8 +152,8 @@ static fem_tuning default_tuning(int op, int dim, int phys, int rule, int dtype)
     const fem_tuning t{FEM_STRATEGY_LANE, 1, 4, 0};  // RESIDUAL, BACKWARD: whole lines (p1_tuning)
     const bool f32 = dtype == FEM_F32;
     if (op == FEM_OP_GEOMETRY) return fem_tuning{FEM_STRATEGY_LANE, 4, 4, 0};
-    if (op == FEM_OP_JACOBIAN || op == FEM_OP_JACOBIAN_P2) {  // store-bound: more waves for the large matrices
-        if (phys == FEM_ELASTICITY) return fem_tuning{FEM_STRATEGY_LANE, 1, 4, 16};
+    if (op == FEM_OP_JACOBIAN || op == FEM_OP_JACOBIAN_P2) {  // store-bound: more waves for the larger P2 matrices
+        if (phys == FEM_ELASTICITY) return op == FEM_OP_JACOBIAN_P2 ? fem_tuning{FEM_STRATEGY_LANE, 1, 4, 16} : fem_tuning{FEM_STRATEGY_LANE, 1, 1, 0};
         return op == FEM_OP_JACOBIAN_P2 ? fem_tuning{FEM_STRATEGY_LANE, 1, 4, 0} : fem_tuning{FEM_STRATEGY_LANE, 1, 2, 0};
     }
     // P3: the 3D elements hold 20-60 closure and output words per lane, and
@@ -612,8 +612,9 @@ fem_status fem_integrate_jacobian(int dim, int physics, int rule, int coef_space
     const int op = order == 1 ? FEM_OP_JACOBIAN : order == 2 ? FEM_OP_JACOBIAN_P2 : FEM_OP_JACOBIAN_P3;
     fem_tuning t = get_tuning(op, dim, physics, rule, dtype);
     // Rows at odd words: four waves per workgroup, XCD by XCD. Whole lines in
-    // launch order (P1 3D elasticity FP64, 400,000 tets: 113 us, 115 us XCD by
-    // XCD; at 400,001 tets 184 us streaming in launch order, 145 us this way).
+    // launch order (P1 3D elasticity FP64, one element per lane: 400,000 tets 113
+    // us, 115 us XCD by XCD; 400,001 tets 184 us streaming in launch order, 145
+    // us this way).
     const bool whole = whole_lines(n_elem, dtype == FEM_F32 ? 4 : 8, {elem_mat});
     if (!whole && is_default(t, op, dim, physics, rule, dtype)) t = fem_tuning{FEM_STRATEGY_LANE, 1, 4, 0};
     JacobianArgs a{n_elem, inv_j, det_j, coef, elem_mat};

@@ -9,8 +9,8 @@
 // Laplacian g3 = kappa delta_ij, elasticity g3 = lambda delta_ci delta_c'j
 // + mu (delta_cc' delta_ij + delta_cj delta_ic'), mass g0 = kappa.
 //
-// One lane per element; every SoA row is one coalesced access per wave, and
-// the output (N_bt^2 rows) dominates the traffic. The rule and coefficient
+// A lane owns V consecutive elements; every SoA row is one coalesced access per
+// wave, and the output (N_bt^2 rows) dominates the traffic. The rule and coefficient
 // space only enter the moments below, so they are uniform run-time
 // arguments of one kernel per (dim, physics, order, dtype). The gradient terms use the
 // barycentric structure of the basis: grad phi_b = sum_v alpha_bv grad lam_v
@@ -24,6 +24,7 @@
 // over the points directly. The matrix is written exactly symmetric: each
 // entry below the diagonal is a copy of its mirror. On small meshes blockIdx.y
 // deals the basis functions out to several workgroups per tile (matrix_parts).
+#include "fem_device.hpp"
 #include "fem_internal.hpp"
 #include "p2_device.hpp"
 
@@ -111,30 +112,32 @@ __device__ __forceinline__ Real moment(const Moments<NV, Real>& M, Aff A, Aff B)
     return s;
 }
 
+// Coefficient words of a space.
+template <int DIM, int RULE, int SPACE>
+constexpr int coef_words() {
+    return SPACE == FEM_COEF_QUAD ? RuleBary<DIM, RULE>::NQ : SPACE == FEM_COEF_P1 ? DIM + 1 : 1;
+}
+
 // Coefficient at the points of the rule, weighted: k[m][q] = w_q |J| a_m(x_q)
-// from the element's words in their space.
-template <int DIM, int RULE, int SPACE, int NCOEF, typename Real>
-__device__ __forceinline__ void weighted_coef(const Real* __restrict__ coef, int64_t n, int64_t e, Real dj,
+// from the words cf[][v] of the lane's element v in their space.
+template <int DIM, int RULE, int SPACE, int NCOEF, int W, typename Real>
+__device__ __forceinline__ void weighted_coef(const Real (&cf)[NCOEF * coef_words<DIM, RULE, SPACE>()][W], int v, Real dj,
                                               Real (&k)[NCOEF][RuleBary<DIM, RULE>::NQ]) {
     using Q = RuleBary<DIM, RULE>;
-    constexpr int NV = DIM + 1, NQ = Q::NQ;
-    constexpr int NW = SPACE == FEM_COEF_QUAD ? NQ : SPACE == FEM_COEF_P1 ? NV : 1;
+    constexpr int NV = DIM + 1, NQ = Q::NQ, NW = coef_words<DIM, RULE, SPACE>();
 #pragma unroll
     for (int m = 0; m < NCOEF; ++m) {
-        Real cf[NW];
-#pragma unroll
-        for (int f = 0; f < NW; ++f) cf[f] = __builtin_nontemporal_load(coef + (int64_t)(m * NW + f) * n + e);
 #pragma unroll
         for (int q = 0; q < NQ; ++q) {
             Real a;
             if constexpr (SPACE == FEM_COEF_QUAD) {
-                a = cf[q];
+                a = cf[m * NW + q][v];
             } else if constexpr (SPACE == FEM_COEF_P1) {
-                a = Real(Q::lam(q, 0)) * cf[0];
+                a = Real(Q::lam(q, 0)) * cf[m * NW][v];
 #pragma unroll
-                for (int v = 1; v < NV; ++v) a = fmadd(Real(Q::lam(q, v)), cf[v], a);
+                for (int w = 1; w < NV; ++w) a = fmadd(Real(Q::lam(q, w)), cf[m * NW + w][v], a);
             } else {
-                a = cf[0];
+                a = cf[m * NW][v];
             }
             k[m][q] = (Real(Q::w(q)) * dj) * a;
         }
@@ -142,13 +145,13 @@ __device__ __forceinline__ void weighted_coef(const Real* __restrict__ coef, int
 }
 
 // Moments of the weighted coefficients (m1, m2 only for second order).
-template <int DIM, int RULE, int SPACE, int NCOEF, int ORDER, typename Real>
-__device__ __forceinline__ void coef_moments(const Real* __restrict__ coef, int64_t n, int64_t e, Real dj,
-                                             Moments<DIM + 1, Real> (&M)[NCOEF]) {
+template <int DIM, int RULE, int SPACE, int NCOEF, int ORDER, int W, typename Real>
+__device__ __forceinline__ void coef_moments(const Real (&cf)[NCOEF * coef_words<DIM, RULE, SPACE>()][W], int lane_elem,
+                                             Real dj, Moments<DIM + 1, Real> (&M)[NCOEF]) {
     using Q = RuleBary<DIM, RULE>;
     constexpr int NV = DIM + 1, NQ = Q::NQ;
     Real k[NCOEF][NQ];
-    weighted_coef<DIM, RULE, SPACE, NCOEF, Real>(coef, n, e, dj, k);
+    weighted_coef<DIM, RULE, SPACE, NCOEF, W, Real>(cf, lane_elem, dj, k);
 #pragma unroll
     for (int m = 0; m < NCOEF; ++m) {
         Real s = k[m][0];
@@ -176,28 +179,43 @@ __device__ __forceinline__ void coef_moments(const Real* __restrict__ coef, int6
     }
 }
 
+// Words e .. e+W-1 of entry (r, s) of a matrix with `size` rows, and of its
+// mirror.
+template <bool STREAM_OUT, typename Real, int W>
+__device__ __forceinline__ void store_entry(const Real (&x)[1][W], int r, int s, int size, Real* __restrict__ out, int64_t n,
+                                            int64_t e) {
+    store_rows_v<1, STREAM_OUT>(out + (int64_t)(r * size + s) * n, n, e, x);
+    if (s != r) store_rows_v<1, STREAM_OUT>(out + (int64_t)(s * size + r) * n, n, e, x);
+}
+
 // Mass matrix K_bb' = sum_q k_q phi_b(x_q) phi_b'(x_q), stored directly.
-template <int DIM, int ORDER, int RULE, int SPACE, bool STREAM_OUT, typename Real>
-__device__ __forceinline__ void mass_matrix(const Real* __restrict__ coef, int64_t n, int64_t e, Real dj,
+template <int DIM, int ORDER, int RULE, int SPACE, bool STREAM_OUT, bool SPLIT, int W, typename Real>
+__device__ __forceinline__ void mass_matrix(const Real* __restrict__ coef, int64_t n, int64_t e, const Real (&dj)[1][W],
                                             Real* __restrict__ out) {
     using Q = RuleBary<DIM, RULE>;
     using Bs = LagBasis<DIM, ORDER>;
-    constexpr int NB = Bs::NB, NQ = Q::NQ;
-    Real k[1][NQ];
-    weighted_coef<DIM, RULE, SPACE, 1, Real>(coef, n, e, dj, k);
+    constexpr int NB = Bs::NB, NQ = Q::NQ, NW = coef_words<DIM, RULE, SPACE>();
+    Real cf[NW][W], k[W][1][NQ];
+    load_rows_v<NW>(coef, n, e, cf);
+#pragma unroll
+    for (int v = 0; v < W; ++v) weighted_coef<DIM, RULE, SPACE, 1, W, Real>(cf, v, fabs(dj[0][v]), k[v]);
     static_for<0, NB>([&](auto b_c) {
         constexpr int b = decltype(b_c)::value;
-        if (b % gridDim.y != blockIdx.y) return;
+        if (SPLIT && b % gridDim.y != blockIdx.y) return;
         static_for<b, NB>([&](auto bp_c) {
             constexpr int bp = decltype(bp_c)::value;
-            Real s = Real(0);
+            Real x[1][W];
 #pragma unroll
-            for (int q = 0; q < NQ; ++q) {
-                auto lam = [q](int v) { return Q::lam(q, v); };
-                s = fmadd(Real(Bs::value(b, lam) * Bs::value(bp, lam)), k[0][q], s);
+            for (int v = 0; v < W; ++v) {
+                Real s = Real(0);
+#pragma unroll
+                for (int q = 0; q < NQ; ++q) {
+                    auto lam = [q](int w) { return Q::lam(q, w); };
+                    s = fmadd(Real(Bs::value(b, lam) * Bs::value(bp, lam)), k[v][0][q], s);
+                }
+                x[0][v] = s;
             }
-            row_st<STREAM_OUT>(s, out + (int64_t)(b * NB + bp) * n + e);
-            if constexpr (bp != b) row_st<STREAM_OUT>(s, out + (int64_t)(bp * NB + b) * n + e);
+            store_entry<STREAM_OUT>(x, b, bp, NB, out, n, e);
         });
     });
 }
@@ -219,7 +237,47 @@ __device__ __forceinline__ void with_scheme(int rule, int space, const F& f) {
     else by_space(std::integral_constant<int, OTHER>());
 }
 
-template <int DIM, int PHYS, int ORDER, bool STREAM_OUT, typename Real>
+// Matrix entries between basis functions b and bp of one element, from its
+// moments, gradients and their products.
+template <int DIM, int PHYS, int ORDER, int b, int bp, int NC, int NCOEF, typename Real>
+__device__ __forceinline__ void matrix_block(const Moments<DIM + 1, Real> (&M)[NCOEF], const Real (&g)[DIM + 1][DIM],
+                                             const Real (&P)[DIM + 1][DIM + 1], Real (&blk)[NC][NC]) {
+    using Bs = LagBasis<DIM, ORDER>;
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int cp = 0; cp < NC; ++cp) blk[c][cp] = Real(0);
+#pragma unroll
+    for (int s = 0; s < Bs::nsupp(b); ++s)
+#pragma unroll
+        for (int t = 0; t < Bs::nsupp(bp); ++t) {
+            const int v = Bs::supp(b, s), w = Bs::supp(bp, t);
+            const Aff A = Bs::alpha(b, s), B = Bs::alpha(bp, t);
+            if constexpr (PHYS == FEM_LAPLACE) {
+                blk[0][0] = fmadd(moment(M[0], A, B), P[v][w], blk[0][0]);
+            } else {
+                const Real lm = moment(M[0], A, B), mu = moment(M[1], A, B);
+#pragma unroll
+                for (int c = 0; c < NC; ++c)
+#pragma unroll
+                    for (int cp = 0; cp < NC; ++cp) {
+                        if (bp == b && cp < c) continue;
+                        Real x = fmadd(lm * g[v][c], g[w][cp], blk[c][cp]);
+                        x = fmadd(mu, g[v][cp] * g[w][c], x);
+                        if (c == cp) x = fmadd(mu, P[v][w], x);
+                        blk[c][cp] = x;
+                    }
+            }
+        }
+}
+
+// SPLIT: blockIdx.y deals out the basis functions. The test of it also keeps
+// one function's arithmetic and stores apart from the next one's. Short rows
+// lose by that, so launches that need no split go without (P2 3D Laplacian
+// FP64, 262,144 tets: 53.0 us with it, 49.9 without); the elasticity blocks of
+// V elements need it (3D FP32, V = 4: 133 registers with it, 271 without,
+// 400,000 tets 54 and 61 us).
+template <int DIM, int PHYS, int ORDER, int V, bool STREAM_OUT, bool SPLIT, typename Real>
 __global__ void __launch_bounds__(256)
 jacobian_kernel(int64_t n, int order, int rule, int space, const Real* __restrict__ inv_j, const Real* __restrict__ det_j,
                 const Real* __restrict__ coef, Real* __restrict__ out) {
@@ -227,99 +285,117 @@ jacobian_kernel(int64_t n, int order, int rule, int space, const Real* __restric
     constexpr int NV = DIM + 1, NB = Bs::NB;
     constexpr int NC = PHYS == FEM_ELASTICITY ? DIM : 1, NBT = NB * NC;
     constexpr int NCOEF = PHYS == FEM_ELASTICITY ? 2 : 1;
+    const int64_t nchunk = (n + V - 1) / V;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t e = row_block(order) * blockDim.x + threadIdx.x; e < n; e += stride) {
-        const Real dj = fabs(__builtin_nontemporal_load(det_j + e));
-        if constexpr (PHYS == FEM_MASS) {
-            with_scheme<DIM, ORDER>(rule, space, [&](auto rule_c, auto space_c) {
-                mass_matrix<DIM, ORDER, decltype(rule_c)::value, decltype(space_c)::value, STREAM_OUT, Real>(coef, n, e, dj, out);
-            });
-        } else {
-            Moments<NV, Real> M[NCOEF];
-            with_scheme<DIM, ORDER>(rule, space, [&](auto rule_c, auto space_c) {
-                coef_moments<DIM, decltype(rule_c)::value, decltype(space_c)::value, NCOEF, ORDER, Real>(coef, n, e,
-                                                                                                        dj, M);
-            });
-            Real ij[DIM * DIM];
-#pragma unroll
-            for (int f = 0; f < DIM * DIM; ++f) ij[f] = __builtin_nontemporal_load(inv_j + f * n + e);
-            // physical barycentric gradients: g_{k+1} = row k of J^{-1}, g_0 = -sum
-            Real g[NV][DIM];
-#pragma unroll
-            for (int i = 0; i < DIM; ++i) {
-                Real s = Real(0);
-#pragma unroll
-                for (int kk = 0; kk < DIM; ++kk) {
-                    g[kk + 1][i] = ij[kk * DIM + i];
-                    s += ij[kk * DIM + i];
-                }
-                g[0][i] = -s;
-            }
-            Real P[NV][NV];  // g_v . g_w
-#pragma unroll
-            for (int v = 0; v < NV; ++v)
-#pragma unroll
-                for (int w = 0; w < NV; ++w) {
-                    if (w < v) continue;
-                    Real s = g[v][0] * g[w][0];
-#pragma unroll
-                    for (int i = 1; i < DIM; ++i) s = fmadd(g[v][i], g[w][i], s);
-                    P[v][w] = s;
-                    P[w][v] = s;
-                }
-            static_for<0, NB>([&](auto b_c) {
-                constexpr int b = decltype(b_c)::value;
-                if (b % gridDim.y != blockIdx.y) return;
-                static_for<b, NB>([&](auto bp_c) {
-                    constexpr int bp = decltype(bp_c)::value;
-                    Real blk[NC][NC];
-#pragma unroll
-                    for (int c = 0; c < NC; ++c)
-#pragma unroll
-                        for (int cp = 0; cp < NC; ++cp) blk[c][cp] = Real(0);
-#pragma unroll
-                    for (int s = 0; s < Bs::nsupp(b); ++s)
-#pragma unroll
-                        for (int t = 0; t < Bs::nsupp(bp); ++t) {
-                            const int v = Bs::supp(b, s), w = Bs::supp(bp, t);
-                            const Aff A = Bs::alpha(b, s), B = Bs::alpha(bp, t);
-                            if constexpr (PHYS == FEM_LAPLACE) {
-                                blk[0][0] = fmadd(moment(M[0], A, B), P[v][w], blk[0][0]);
-                            } else {
-                                const Real lm = moment(M[0], A, B), mu = moment(M[1], A, B);
-#pragma unroll
-                                for (int c = 0; c < NC; ++c)
-#pragma unroll
-                                    for (int cp = 0; cp < NC; ++cp) {
-                                        if (bp == b && cp < c) continue;
-                                        Real x = fmadd(lm * g[v][c], g[w][cp], blk[c][cp]);
-                                        x = fmadd(mu, g[v][cp] * g[w][c], x);
-                                        if (c == cp) x = fmadd(mu, P[v][w], x);
-                                        blk[c][cp] = x;
-                                    }
-                            }
-                        }
-#pragma unroll
-                    for (int c = 0; c < NC; ++c)
-#pragma unroll
-                        for (int cp = 0; cp < NC; ++cp) {
-                            if (bp == b && cp < c) continue;
-                            const int r = b * NC + c, s = bp * NC + cp;
-                            row_st<STREAM_OUT>(blk[c][cp], out + (int64_t)(r * NBT + s) * n + e);
-                            if (s != r) row_st<STREAM_OUT>(blk[c][cp], out + (int64_t)(s * NBT + r) * n + e);
-                        }
+    for (int64_t ch = row_block(order) * blockDim.x + threadIdx.x; ch < nchunk; ch += stride) {
+        for_chunk<V>(ch * V, n, [&](auto width, int64_t e) {
+            constexpr int W = decltype(width)::value;
+            Real dj[1][W];
+            load_rows_v<1>(det_j, n, e, dj);
+            if constexpr (PHYS == FEM_MASS) {
+                with_scheme<DIM, ORDER>(rule, space, [&](auto rule_c, auto space_c) {
+                    mass_matrix<DIM, ORDER, decltype(rule_c)::value, decltype(space_c)::value, STREAM_OUT, SPLIT, W, Real>(
+                        coef, n, e, dj, out);
                 });
-            });
-        }
+            } else {
+                Moments<NV, Real> M[W][NCOEF];
+                with_scheme<DIM, ORDER>(rule, space, [&](auto rule_c, auto space_c) {
+                    constexpr int R = decltype(rule_c)::value, S = decltype(space_c)::value;
+                    Real cf[NCOEF * coef_words<DIM, R, S>()][W];
+                    load_rows_v<NCOEF * coef_words<DIM, R, S>()>(coef, n, e, cf);
+#pragma unroll
+                    for (int v = 0; v < W; ++v)
+                        coef_moments<DIM, R, S, NCOEF, ORDER, W, Real>(cf, v, fabs(dj[0][v]), M[v]);
+                });
+                Real ij[DIM * DIM][W];
+                load_rows_v<DIM * DIM>(inv_j, n, e, ij);
+                Real g[W][NV][DIM];  // physical barycentric gradients: g_{k+1} = row k of J^{-1}, g_0 = -sum
+                Real P[W][NV][NV];   // g_v . g_w
+#pragma unroll
+                for (int x = 0; x < W; ++x) {
+#pragma unroll
+                    for (int i = 0; i < DIM; ++i) {
+                        Real s = Real(0);
+#pragma unroll
+                        for (int kk = 0; kk < DIM; ++kk) {
+                            g[x][kk + 1][i] = ij[kk * DIM + i][x];
+                            s += ij[kk * DIM + i][x];
+                        }
+                        g[x][0][i] = -s;
+                    }
+#pragma unroll
+                    for (int v = 0; v < NV; ++v)
+#pragma unroll
+                        for (int w = 0; w < NV; ++w) {
+                            if (w < v) continue;
+                            Real s = g[x][v][0] * g[x][w][0];
+#pragma unroll
+                            for (int i = 1; i < DIM; ++i) s = fmadd(g[x][v][i], g[x][w][i], s);
+                            P[x][v][w] = s;
+                            P[x][w][v] = s;
+                        }
+                }
+                static_for<0, NB>([&](auto b_c) {
+                    constexpr int b = decltype(b_c)::value;
+                    if (SPLIT && b % gridDim.y != blockIdx.y) return;
+                    static_for<b, NB>([&](auto bp_c) {
+                        constexpr int bp = decltype(bp_c)::value;
+                        Real blk[W][NC][NC];
+#pragma unroll
+                        for (int x = 0; x < W; ++x)
+                            matrix_block<DIM, PHYS, ORDER, b, bp, NC, NCOEF, Real>(M[x], g[x], P[x], blk[x]);
+#pragma unroll
+                        for (int c = 0; c < NC; ++c)
+#pragma unroll
+                            for (int cp = 0; cp < NC; ++cp) {
+                                if (bp == b && cp < c) continue;
+                                Real x[1][W];
+#pragma unroll
+                                for (int v = 0; v < W; ++v) x[0][v] = blk[v][c][cp];
+                                store_entry<STREAM_OUT>(x, b * NC + c, bp * NC + cp, NBT, out, n, e);
+                            }
+                    });
+                });
+            }
+        });
     }
 }
 
+// Elements per lane, V: 16 bytes of every row for P1, where the matrices are
+// short enough for V sets of moments and gradients in the registers.
+//  - Elasticity, as long as that leaves a wave per SIMD. Odd words, four waves
+//    per workgroup: 3D FP32, 1,000,001 tets 190 us with V = 1, 159 with 4;
+//    FP64, 200,001 tets 75 and 64. Whole lines: 3D FP32, 400,000 tets 61 and
+//    54; FP64 112 and 107 (518 MB, 4.8 TB/s).
+//  - Laplacian and mass FP32 at odd words, as long as that leaves two: 3D,
+//    1,000,001 tets 26.8 and 24.4 us, mass 20.4 and 18.3; but 300,001 tets 9.2
+//    and 11.2. Whole lines lose (FP64, 2^20 tets 46 and 52), FP64 at odd words
+//    is the same.
 template <int DIM, int PHYS, int ORDER, typename Real>
 static hipError_t launch_jac(int rule, int space, const JacobianArgs& a, const Launch& l) {
-    const auto k = l.stream_out ? jacobian_kernel<DIM, PHYS, ORDER, true, Real> : jacobian_kernel<DIM, PHYS, ORDER, false, Real>;
-    hipLaunchKernelGGL(k, dim3(l.grid, matrix_parts(l, LagBasis<DIM, ORDER>::NB)), dim3(l.block), 0, l.stream, a.n, l.order, rule, space, static_cast<const Real*>(a.inv_j), static_cast<const Real*>(a.det_j),
-                       static_cast<const Real*>(a.coef), static_cast<Real*>(a.out));
-    return hipGetLastError();
+    constexpr bool ELAST = PHYS == FEM_ELASTICITY;
+    constexpr int V = ORDER == 1 && (ELAST || sizeof(Real) == 4) ? 16 / (int)sizeof(Real) : 1;
+    Launch m = l;
+    auto go = [&](auto k, int parts) {
+        hipLaunchKernelGGL(k, dim3(m.grid, parts), dim3(m.block), 0, m.stream, a.n, m.order, rule, space,
+                           static_cast<const Real*>(a.inv_j), static_cast<const Real*>(a.det_j),
+                           static_cast<const Real*>(a.coef), static_cast<Real*>(a.out));
+        return hipGetLastError();
+    };
+    if constexpr (V > 1) {
+        if (a.n >= (int64_t)V * 64 * (ELAST ? 1024 : 2048) && (ELAST || !l.stream_out)) {
+            m.grid = (l.grid + V - 1) / V;
+            const int parts = ELAST ? matrix_parts(m, LagBasis<DIM, ORDER>::NB) : 1;
+            if constexpr (ELAST) {
+                if (l.stream_out) return go(jacobian_kernel<DIM, PHYS, ORDER, V, true, true, Real>, parts);
+            }
+            return go(jacobian_kernel<DIM, PHYS, ORDER, V, false, ELAST, Real>, parts);
+        }
+    }
+    const int parts = matrix_parts(l, LagBasis<DIM, ORDER>::NB);
+    if (parts > 1) return go(jacobian_kernel<DIM, PHYS, ORDER, 1, false, true, Real>, parts);
+    return l.stream_out ? go(jacobian_kernel<DIM, PHYS, ORDER, 1, true, false, Real>, 1)
+                        : go(jacobian_kernel<DIM, PHYS, ORDER, 1, false, false, Real>, 1);
 }
 
 // Runtime (dim, physics, order, dtype) to a kernel instance; (rule, space)

@@ -179,3 +179,16 @@ def test_matrix_parts(dim, physics, order, dtype, n):
         part = [t[..., lo:hi].contiguous() for t in (ij, dj, coef)]
         ref = api.fem_integrate_jacobian(dim, physics, RULES[dim, order], *part, order=order)
         assert torch.equal(got[..., lo:hi], ref)
+
+
+# P1 matrices take 16 bytes per lane from 64 * 1024 (elasticity) or 64 * 2048
+# (FP32 scalar forms at odd words) lanes on: both sides of either limit
+@pytest.mark.parametrize("dtype", DTYPES)
+@pytest.mark.parametrize("dim,physics", [(2, mg.ELASTICITY), (3, mg.ELASTICITY), (3, mg.LAPLACE), (2, mg.MASS)])
+@pytest.mark.parametrize("n", [131071, 131073, 262143, 262144, 262147, 524287, 524290, 524291])
+def test_matrix_vector_width(dim, physics, dtype, n):
+    ij, dj, _, _, coef = _inputs(dim, physics, RULES[dim, 1], 1, n, dtype)
+    got = api.fem_integrate_jacobian(dim, physics, RULES[dim, 1], ij, dj, coef)
+    for lo, hi in ((0, 70), (n // 2, n // 2 + 300), (n - 70, n)):
+        part = [t[..., lo:hi].contiguous() for t in (ij, dj, coef)]
+        assert torch.equal(got[..., lo:hi], api.fem_integrate_jacobian(dim, physics, RULES[dim, 1], *part))

@@ -115,13 +115,21 @@ __device__ __forceinline__ void unroll_for(const F& f) {
 // (centroid; a high coordinate at one vertex; at both vertices of an edge), and as a
 // function of the point du/dlam_v takes only a few shapes: its coefficients
 // depend on lam_v and, at one other vertex p, on whether lam_p differs from
-// the remaining two. So with the sums over the other vertices o
-//   A = sum_o u(node near v on edge vo),  B = sum_o u(node near o),
-//   F = sum of u over the faces at v,
-// five combinations of (u_v, A, B, F) serve all eleven points, six of them
-// after a correction of three terms in the words of vertex p alone: 53
-// operations per v and component, where the products of the tabulated
-// derivatives take 110. The basis phase is the transpose.
+// the remaining two. The words of those two vertices share their coefficients,
+// so they enter as pair sums, which serve every point: with
+//   a_o = u(node near v on edge vo), b_o = u(node near o), f_o = u(face without o)
+// a derivative takes u_v, the three pair sums and the three words of p, and at
+// the centroid and at v's own vertex point u_v and the sums over all three: 77
+// operations per v and component for all eleven points, where the products of
+// the tabulated derivatives take 110. The basis phase is the transpose.
+// Every word is multiplied by its own entry of the derivative table, as in the
+// tabulated form, so nothing cancels that does not cancel there, and the terms
+// are summed in orders that keep the partial sums small (small coefficients
+// first, and a pair's next to the opposite ones). RMS rounding of the residual
+// relative to the tabulated form's, both types: 0.73-0.93 over independent,
+// constant plus independent, linear and smooth nodal fields, of dcoef 0.73-0.98.
+// (Sums over all three vertices with the words of p as corrections take 53
+// operations but cancel: 1.1-1.3 on linear and smooth fields.)
 struct P3Tet {
     using Q = RuleP2<3, FEM_RULE_TET11>;
     // node of edge (v, o) near v; face without vertex p
@@ -129,83 +137,84 @@ struct P3Tet {
         return 4 + 2 * ElemP2<3, 0, 0, 0>::edge_of(v, o) + (v < o ? 0 : 1);
     }
     __host__ __device__ static constexpr int face_without(int p) { return 19 - p; }
-    // k-th vertex other than v, and the vertex left over beside v and p, p'
+    // k-th vertex other than v
     __host__ __device__ static constexpr int other(int v, int k) { return k < v ? k : k + 1; }
     __host__ __device__ static constexpr int edge_point(int a, int b) { return 5 + ElemP2<3, 0, 0, 0>::edge_of(a, b); }
     // the edge that joins the two vertices other than a and b
     __host__ __device__ static constexpr int opposite_point(int a, int b) {
         return 5 + (5 - ElemP2<3, 0, 0, 0>::edge_of(a, b));
     }
-    // The combinations: 0 centroid; 1 v's own vertex point; 2 another vertex
+    // The shapes of du/dlam_v: 0 centroid; 1 v's own vertex point; 2 another vertex
     // point (p high); 3 an edge point at v (p the other end); 4 an edge point
-    // away from v (p the other low vertex). Their coefficients of u_v, A, B, F
-    // (j = 0..3) are entries of the derivative table at v = 0, and the
-    // corrections in u(node near v on vp), u(node near p), u(face without p)
-    // the differences of two entries, so both forms share the table's
-    // roundings: relative to extended precision an FP64 residual of 3D elasticity
-    // is off by 3.0e-16 (3.5e-16 with the products of the table).
-    static constexpr int point(int k) { return k == 0 ? 0 : k == 1 ? 1 : k == 2 ? 2 : k == 3 ? edge_point(0, 1) : edge_point(2, 3); }
-    static constexpr double base(int k, int j) {
-        return P3Basis<3, FEM_RULE_TET11>::dl(point(k), j == 0 ? 0 : j == 1 ? edge_node(0, 2) : j == 2 ? edge_node(2, 0)
-                                                                                              : face_without(3), 0);
+    // away from v (p the other low vertex).
+    __host__ __device__ static constexpr int point(int k, int v, int p) {
+        return k == 0 ? 0 : k == 1 ? 1 + v : k == 2 ? 1 + p : k == 3 ? edge_point(v, p) : opposite_point(v, p);
     }
-    // of combinations 2..4, with p = 1
-    static constexpr double corr(int k, int j) {
-        return P3Basis<3, FEM_RULE_TET11>::dl(point(k), j == 0 ? edge_node(0, 1) : j == 1 ? edge_node(1, 0) : face_without(1), 0) -
-               base(k, j + 1);
+    // Their coefficients, entries of the derivative table at v = 0 and p = 1: of
+    // u_v (j = 0) and of a, b, f of the vertices that share one (j = 1..3),
+    static constexpr double base(int k, int j) {
+        return P3Basis<3, FEM_RULE_TET11>::dl(point(k, 0, 1), j == 0 ? 0 : j == 1 ? edge_node(0, 2) : j == 2 ? edge_node(2, 0)
+                                                                                                    : face_without(3), 0);
+    }
+    // and of a, b, f of p (j = 1..3, shapes 2..4)
+    static constexpr double own(int k, int j) {
+        return P3Basis<3, FEM_RULE_TET11>::dl(point(k, 0, 1), j == 1 ? edge_node(0, 1) : j == 2 ? edge_node(1, 0) : face_without(1), 0);
+    }
+    // Order of the six terms after u_v in shapes 2..4: 1..3 the pair sums of a,
+    // b, f, 4..6 p's own.
+    static constexpr int term(int k, int i) {
+        constexpr int order[3][6] = {{1, 6, 4, 3, 2, 5}, {5, 6, 2, 1, 3, 4}, {4, 5, 2, 1, 3, 6}};
+        return order[k - 2][i];
     }
 
     // Physical gradient of one component at every point: u[b * NC] its words,
     // ij the inverse Jacobian; sink(q constant, gradient).
     template <int NC, typename Real, typename Sink>
     __device__ static __forceinline__ void gradients(const Real* u, const Real* ij, const Sink& sink) {
-        Real bs[4][5];
+        Real d[11][4];
         unroll_for<0, 4>([&](auto v_c) {
             constexpr int v = decltype(v_c)::value;
             constexpr int o0 = other(v, 0), o1 = other(v, 1), o2 = other(v, 2);
-            const Real a = (u[edge_node(v, o0) * NC] + u[edge_node(v, o1) * NC]) + u[edge_node(v, o2) * NC];
-            const Real b = (u[edge_node(o0, v) * NC] + u[edge_node(o1, v) * NC]) + u[edge_node(o2, v) * NC];
-            const Real f = (u[face_without(o0) * NC] + u[face_without(o1) * NC]) + u[face_without(o2) * NC];
-            unroll_for<0, 5>([&](auto k_c) {
+            // x[j - 1]: a, b, f of the other vertices; y: their pair sums
+            const Real x[3][3] = {{u[edge_node(v, o0) * NC], u[edge_node(v, o1) * NC], u[edge_node(v, o2) * NC]},
+                                  {u[edge_node(o0, v) * NC], u[edge_node(o1, v) * NC], u[edge_node(o2, v) * NC]},
+                                  {u[face_without(o0) * NC], u[face_without(o1) * NC], u[face_without(o2) * NC]}};
+            Real y[3][3], z[3];
+#pragma unroll
+            for (int j = 0; j < 3; ++j) {
+                y[j][0] = x[j][1] + x[j][2];
+                y[j][1] = x[j][2] + x[j][0];
+                y[j][2] = x[j][0] + x[j][1];
+                z[j] = y[j][0] + x[j][0];
+            }
+            constexpr double c0 = base(0, 0), c1 = base(0, 1), c2 = base(0, 2), c3 = base(0, 3);
+            d[0][v] = fmadd(Real(c3), z[2], fmadd(Real(c1), z[0], fmadd(Real(c2), z[1], Real(c0) * u[v * NC])));
+            constexpr double v0 = base(1, 0), v1 = base(1, 1), v2 = base(1, 2), v3 = base(1, 3);
+            d[1 + v][v] = fmadd(Real(v0), u[v * NC], fmadd(Real(v1), z[0], fmadd(Real(v2), z[1], Real(v3) * z[2])));
+            unroll_for<2, 5>([&](auto k_c) {
                 constexpr int k = decltype(k_c)::value;
-                constexpr double c0 = base(k, 0), c1 = base(k, 1), c2 = base(k, 2), c3 = base(k, 3);
-                bs[v][k] = fmadd(Real(c3), f, fmadd(Real(c2), b, fmadd(Real(c1), a, Real(c0) * u[v * NC])));
+                constexpr double b0 = base(k, 0);
+                const Real t = Real(b0) * u[v * NC];
+                unroll_for<0, 3>([&](auto n_c) {
+                    constexpr int n = decltype(n_c)::value;
+                    Real s = t;
+                    unroll_for<0, 6>([&](auto i_c) {
+                        constexpr int j = term(k, decltype(i_c)::value);
+                        constexpr double c = j < 4 ? base(k, j) : own(k, j - 3);
+                        s = fmadd(Real(c), j < 4 ? y[(j - 1) % 3][n] : x[(j - 1) % 3][n], s);
+                    });
+                    d[point(k, v, other(v, n))][v] = s;
+                });
             });
         });
-        auto at = [&](auto v_c, auto p_c, auto k_c) {
-            constexpr int v = decltype(v_c)::value, p = decltype(p_c)::value, k = decltype(k_c)::value;
-            constexpr double c0 = corr(k, 0), c1 = corr(k, 1), c2 = corr(k, 2);
-            return fmadd(Real(c2), u[face_without(p) * NC],
-                         fmadd(Real(c1), u[edge_node(p, v) * NC], fmadd(Real(c0), u[edge_node(v, p) * NC], bs[v][k])));
-        };
-        auto emit = [&](auto q_c, const Real (&d)[4]) {
+        unroll_for<0, 11>([&](auto q_c) {
+            constexpr int q = decltype(q_c)::value;
             Real g[3];
 #pragma unroll
             for (int i = 0; i < 3; ++i)
-                g[i] = fmadd(d[3], ij[6 + i], fmadd(d[2], ij[3 + i], fmadd(d[1], ij[i], d[0] * -((ij[i] + ij[3 + i]) + ij[6 + i]))));
+                g[i] = fmadd(d[q][3], ij[6 + i],
+                             fmadd(d[q][2], ij[3 + i], fmadd(d[q][1], ij[i], d[q][0] * -((ij[i] + ij[3 + i]) + ij[6 + i]))));
             sink(q_c, g);
-        };
-        unroll_for<0, 11>([&](auto q_c) {
-            constexpr int q = decltype(q_c)::value;
-            Real d[4];
-            unroll_for<0, 4>([&](auto v_c) {
-                constexpr int v = decltype(v_c)::value;
-                if constexpr (q == 0) {
-                    d[v] = bs[v][0];
-                } else if constexpr (q < 5) {
-                    constexpr int p = q - 1;
-                    if constexpr (p == v) d[v] = bs[v][1];
-                    else d[v] = at(v_c, std::integral_constant<int, p>(), std::integral_constant<int, 2>());
-                } else {
-                    constexpr int i = Q::edge_i(q - 5), j = Q::edge_j(q - 5);
-                    if constexpr (v == i || v == j) {
-                        d[v] = at(v_c, std::integral_constant<int, i + j - v>(), std::integral_constant<int, 3>());
-                    } else {
-                        d[v] = at(v_c, std::integral_constant<int, 6 - i - j - v>(), std::integral_constant<int, 4>());
-                    }
-                }
-            });
-            emit(q_c, d);
         });
     }
 
@@ -223,29 +232,34 @@ struct P3Tet {
         });
         unroll_for<0, 4>([&](auto v_c) {
             constexpr int v = decltype(v_c)::value;
-            constexpr int o0 = other(v, 0), o1 = other(v, 1), o2 = other(v, 2);
-            const Real e[5] = {h[0][v], h[1 + v][v], (h[1 + o0][v] + h[1 + o1][v]) + h[1 + o2][v],
-                               (h[edge_point(v, o0)][v] + h[edge_point(v, o1)][v]) + h[edge_point(v, o2)][v],
-                               (h[opposite_point(v, o0)][v] + h[opposite_point(v, o1)][v]) + h[opposite_point(v, o2)][v]};
-            Real t[4];
-            unroll_for<0, 4>([&](auto j_c) {
-                constexpr int j = decltype(j_c)::value;
-                constexpr double c0 = base(0, j), c1 = base(1, j), c2 = base(2, j), c3 = base(3, j), c4 = base(4, j);
-                t[j] = fmadd(Real(c4), e[4], fmadd(Real(c3), e[3], fmadd(Real(c2), e[2], fmadd(Real(c1), e[1], Real(c0) * e[0]))));
+            // x[k - 2]: h at the shape's points, y: pair sums, z: the sum of all three
+            Real x[3][3], y[3][3], z[3];
+            unroll_for<0, 3>([&](auto k_c) {
+                constexpr int k = decltype(k_c)::value;
+                x[k][0] = h[point(k + 2, v, other(v, 0))][v];
+                x[k][1] = h[point(k + 2, v, other(v, 1))][v];
+                x[k][2] = h[point(k + 2, v, other(v, 2))][v];
+                y[k][0] = x[k][1] + x[k][2];
+                y[k][1] = x[k][2] + x[k][0];
+                y[k][2] = x[k][0] + x[k][1];
+                z[k] = y[k][0] + x[k][0];
             });
-            r[v] = t[0];
-            unroll_for<0, 3>([&](auto n_c) {
-                constexpr int p = other(v, decltype(n_c)::value);
-                const Real hp[3] = {h[1 + p][v], h[edge_point(v, p)][v], h[opposite_point(v, p)][v]};
-                unroll_for<0, 3>([&](auto j_c) {
-                    constexpr int j = decltype(j_c)::value;
-                    constexpr int b = j == 0 ? edge_node(v, p) : j == 1 ? edge_node(p, v) : face_without(p);
+            constexpr double c0 = base(0, 0), c1 = base(1, 0), c2 = base(2, 0), c3 = base(3, 0), c4 = base(4, 0);
+            r[v] = fmadd(Real(c1), h[1 + v][v], fmadd(Real(c3), z[1], fmadd(Real(c2), z[0], fmadd(Real(c4), z[2], Real(c0) * h[0][v]))));
+            unroll_for<1, 4>([&](auto j_c) {
+                constexpr int j = decltype(j_c)::value;
+                constexpr double b0 = base(0, j), b1 = base(1, j), b2 = base(2, j), b3 = base(3, j), b4 = base(4, j);
+                constexpr double w2 = own(2, j), w3 = own(3, j), w4 = own(4, j);
+                const Real t = fmadd(Real(b0), h[0][v], Real(b1) * h[1 + v][v]);
+                unroll_for<0, 3>([&](auto n_c) {
+                    constexpr int n = decltype(n_c)::value, p = other(v, n);
+                    constexpr int b = j == 1 ? edge_node(v, p) : j == 2 ? edge_node(p, v) : face_without(p);
                     // an edge node is met at both its vertices, a face at its three
-                    constexpr bool first = j < 2 ? v < p : v == (p == 0 ? 1 : 0);
-                    constexpr double c2 = corr(2, j), c3 = corr(3, j), c4 = corr(4, j);
-                    Real x = t[j + 1];
-                    if constexpr (!first) x += r[b];
-                    r[b] = fmadd(Real(c4), hp[2], fmadd(Real(c3), hp[1], fmadd(Real(c2), hp[0], x)));
+                    constexpr bool first = j < 3 ? v < p : v == (p == 0 ? 1 : 0);
+                    const Real s = fmadd(Real(b4), y[2][n], fmadd(Real(b3), y[1][n], fmadd(Real(b2), y[0][n], t)));
+                    const Real e = fmadd(Real(w4), x[2][n], fmadd(Real(w3), x[1][n], fmadd(Real(w2), x[0][n], s)));
+                    if constexpr (first) r[b] = e;
+                    else r[b] += e;
                 });
             });
         });

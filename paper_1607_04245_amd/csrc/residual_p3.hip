@@ -10,14 +10,16 @@
 // instead of spilling to memory.
 //
 // Tetrahedra with a gradient term go through their point orbits (P3Tet): 3D
-// elasticity takes about 2300 vector instructions and 153 registers in FP32,
-// 307 in FP64, where the tabulated products took 4000, 178 and 395; so three
-// waves fit a SIMD in FP32. FP32, 600,032 tets, 365 MB: 92 -> 64 us (floor 57);
-// FP64, 2^20 tets, 1.28 GB: 284 -> 234 us (floor 198), one wave per SIMD. Their
+// elasticity takes about 2900 vector instructions and 160 registers in FP32,
+// 327 in FP64, where the tabulated products took 4000, 178 and 395; so three
+// waves fit a SIMD in FP32. FP32, 600,032 tets, 365 MB: 91 -> 68 us (floor 57);
+// FP64, 2^20 tets, 1.28 GB: 283 -> 248 us (floor 198), one wave per SIMD. Their
 // adjoint holds the gradient of w once for both outputs and takes u component
-// by component (173 registers, and 348 with 40 of them spilled to the
-// accumulation registers; 209, and 512 with spills to memory before): 137 ->
-// 108 us and 311 -> 222 us at 600,032 tets (floors 109 and 219).
+// by component (218 registers, and 407 with 38 of them spilled to the
+// accumulation registers; 209, and 512 with spills to memory before): 131 ->
+// 112 us and 310 -> 237 us at 600,032 tets (floors 109 and 219). Rows at odd words,
+// 600,011 tets: residual 152 -> 73 and 219 -> 168 us, adjoint 225 -> 137 and 354 ->
+// 259 us, most of it by their stores and workgroup order.
 #include "fem_internal.hpp"
 #include "p3_device.hpp"
 

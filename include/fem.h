@@ -463,7 +463,9 @@ typedef struct fem_tuning {
                           * and word alignment; GEOMETRY,
                           * RESIDUAL_MESH and RESIDUAL_GATHER (1, 2, 4) give each lane that
                           * many elements 64 apart, to overlap their dependent vertex
-                          * gathers; the P2 and element-matrix ops take 1 */
+                          * gathers; the P2, P3 and element-matrix ops take 1 (the
+                          * P1 element-matrix kernels give a lane 16 bytes of every
+                          * row by themselves where the mesh is large enough) */
     int waves_per_block; /* 1, 2, 4 or 8 (wave64; at most 4 for the P2 and
                           * element-matrix ops) */
     int blocks_per_cu;   /* persistent grid = blocks_per_cu * CUs; 0 = one pass, no grid stride */
@@ -471,9 +473,10 @@ typedef struct fem_tuning {
 
 /* The configuration used for (op, dim, physics, rule, dtype), for every
  * coefficient space: the last one set or tuned in this process, else a
- * built-in default. The built-in default of RESIDUAL and BACKWARD takes more
- * elements per lane, that of the element matrices four waves, where rows
- * start off the 128-byte lines. */
+ * built-in default. One that was set, tuned or loaded is used as it is at every
+ * count, also where it has the default's values; the built-in default of
+ * RESIDUAL and BACKWARD takes more elements per lane, that of the element
+ * matrices four waves, where rows start off the 128-byte lines. */
 fem_status fem_get_tuning(int op, int dim, int physics, int rule, int dtype, fem_tuning* out);
 /* Override the configuration for (op, dim, physics, rule, dtype) in this process. */
 fem_status fem_set_tuning(int op, int dim, int physics, int rule, int dtype, const fem_tuning* t);

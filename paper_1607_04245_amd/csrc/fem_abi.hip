@@ -147,7 +147,8 @@ static TuneKey tune_key(int op, int dim, int phys, int rule, int dtype) {
 
 // Built-in launch configurations: the winners of the autotuner's sweep on
 // one MI355X for the benchmark workloads; other combinations use the robust
-// middle choice. p1_tuning and set_rows refine them by count and alignment.
+// middle choice. Where none was set or tuned, p1_tuning and the element
+// matrices refine them by count and alignment.
 static fem_tuning default_tuning(int op, int dim, int phys, int rule, int dtype) {
     const fem_tuning t{FEM_STRATEGY_LANE, 1, 4, 0};  // RESIDUAL, BACKWARD: whole lines (p1_tuning)
     const bool f32 = dtype == FEM_F32;
@@ -221,25 +222,23 @@ static void load_env_cache() {
     g_env_cache.store(2, std::memory_order_release);
 }
 
-fem_tuning get_tuning(int op, int dim, int phys, int rule, int dtype) {
+fem_tuning get_tuning(int op, int dim, int phys, int rule, int dtype, bool* chosen) {
     load_env_cache();
     std::lock_guard<std::mutex> lock(g_tune_mu);
     auto it = g_tune.find(tune_key(op, dim, phys, rule, dtype));
+    if (chosen) *chosen = it != g_tune.end();
     return it != g_tune.end() ? it->second : default_tuning(op, dim, phys, rule, dtype);
+}
+
+void drop_tuning(int op, int dim, int phys, int rule, int dtype) {
+    std::lock_guard<std::mutex> lock(g_tune_mu);
+    g_tune.erase(tune_key(op, dim, phys, rule, dtype));
 }
 
 void put_tuning(int op, int dim, int phys, int rule, int dtype, const fem_tuning& t) {
     load_env_cache();
     std::lock_guard<std::mutex> lock(g_tune_mu);
     g_tune[tune_key(op, dim, phys, rule, dtype)] = t;
-}
-
-// Whether t is the built-in configuration, which the row rules below refine
-// by size and alignment; any other one is used as it is.
-static bool is_default(const fem_tuning& t, int op, int dim, int phys, int rule, int dtype) {
-    const fem_tuning d = default_tuning(op, dim, phys, rule, dtype);
-    return t.strategy == d.strategy && t.vec == d.vec && t.waves_per_block == d.waves_per_block &&
-           t.blocks_per_cu == d.blocks_per_cu;
 }
 
 // Words per element that an order-k residual reads and writes as rows: the
@@ -274,7 +273,7 @@ static void set_rows(Launch& l, bool whole, int64_t bytes) {
     l.order = !whole || bytes >= (int64_t)192 << 20 ? kOrderXcd : kOrderRuns;
 }
 
-// Configuration of the P1 lane kernels for n elements. Rows at odd words take
+// Built-in configuration of the P1 lane kernels for n elements. Rows at odd words take
 // 16 bytes per lane (four FP32 or two FP64 elements), so that a wave shares 2
 // of its 9 lines with its neighbours and not 2 of 3 (FP32), as long as that
 // leaves two waves per SIMD: P1 3D Laplacian FP32, 1,500,001 tets, 25.1 us with
@@ -292,15 +291,12 @@ static Launch make_launch(const fem_tuning& t, int64_t work_items, int vec, hipS
     l.vec = vec;
     l.block = 64 * t.waves_per_block;
     l.stream = s;
-    int64_t need = (work_items + l.block - 1) / l.block;
-    if (need < 1) need = 1;
+    l.max_grid = 1 << 22;  // the grid-stride loop covers the rest
     if (t.blocks_per_cu > 0) {
         int cus = device_cus();
-        int64_t cap = (int64_t)t.blocks_per_cu * (cus > 0 ? cus : 256);
-        if (need > cap) need = cap;
+        l.max_grid = std::min(l.max_grid, t.blocks_per_cu * (cus > 0 ? cus : 256));
     }
-    if (need > (1 << 22)) need = 1 << 22;  // the grid-stride loop covers the rest
-    l.grid = (int)need;
+    l.grid = grid_for_lanes(l, work_items);
     return l;
 }
 
@@ -398,7 +394,8 @@ fem_status fem_integrate_residual(int dim, int physics, int rule, int coef_space
         set_error("fem_integrate_residual: NULL array");
         return FEM_ERR_INVALID_ARG;
     }
-    fem_tuning t = get_tuning(FEM_OP_RESIDUAL, dim, physics, rule, dtype);
+    bool chosen;
+    fem_tuning t = get_tuning(FEM_OP_RESIDUAL, dim, physics, rule, dtype, &chosen);
     ResidualArgs a{n_elem, inv_j, det_j, u, coef, elem_vec};
     hipError_t e;
     if (t.strategy == FEM_STRATEGY_TRANSPOSE) {
@@ -417,7 +414,7 @@ fem_status fem_integrate_residual(int dim, int physics, int rule, int coef_space
     } else {
         const size_t word = dtype == FEM_F32 ? 4 : 8;
         const bool whole = whole_lines(n_elem, word, {elem_vec});
-        if (is_default(t, FEM_OP_RESIDUAL, dim, physics, rule, dtype)) t = p1_tuning(t, dtype, n_elem, whole);
+        if (!chosen) t = p1_tuning(t, dtype, n_elem, whole);
         Launch l = make_launch(t, (n_elem + t.vec - 1) / t.vec, t.vec, static_cast<hipStream_t>(stream));
         set_rows(l, whole, n_elem * (int64_t)word * row_words(dim, physics, rule, coef_space, 1, 2, 1));
         e = launch_residual_lane(dim, physics, rule, coef_space, dtype, a, l);
@@ -482,10 +479,11 @@ fem_status fem_integrate_residual_backward(int dim, int physics, int rule, int c
         set_error("fem_integrate_residual_backward: NULL array");
         return FEM_ERR_INVALID_ARG;
     }
-    fem_tuning t = get_tuning(FEM_OP_BACKWARD, dim, physics, rule, dtype);
+    bool chosen;
+    fem_tuning t = get_tuning(FEM_OP_BACKWARD, dim, physics, rule, dtype, &chosen);
     const size_t word = dtype == FEM_F32 ? 4 : 8;
     const bool whole = whole_lines(n_elem, word, {du, dcoef});
-    if (is_default(t, FEM_OP_BACKWARD, dim, physics, rule, dtype)) t = p1_tuning(t, dtype, n_elem, whole);
+    if (!chosen) t = p1_tuning(t, dtype, n_elem, whole);
     BackwardArgs a{n_elem, inv_j, det_j, u, coef, w, du, dcoef};
     Launch l = make_launch(t, (n_elem + t.vec - 1) / t.vec, t.vec, static_cast<hipStream_t>(stream));
     set_rows(l, whole, n_elem * (int64_t)word *
@@ -610,13 +608,14 @@ fem_status fem_integrate_jacobian(int dim, int physics, int rule, int coef_space
         return FEM_ERR_INVALID_ARG;
     }
     const int op = order == 1 ? FEM_OP_JACOBIAN : order == 2 ? FEM_OP_JACOBIAN_P2 : FEM_OP_JACOBIAN_P3;
-    fem_tuning t = get_tuning(op, dim, physics, rule, dtype);
+    bool chosen;
+    fem_tuning t = get_tuning(op, dim, physics, rule, dtype, &chosen);
     // Rows at odd words: four waves per workgroup, XCD by XCD. Whole lines in
     // launch order (P1 3D elasticity FP64, one element per lane: 400,000 tets 113
     // us, 115 us XCD by XCD; 400,001 tets 184 us streaming in launch order, 145
     // us this way).
     const bool whole = whole_lines(n_elem, dtype == FEM_F32 ? 4 : 8, {elem_mat});
-    if (!whole && is_default(t, op, dim, physics, rule, dtype)) t = fem_tuning{FEM_STRATEGY_LANE, 1, 4, 0};
+    if (!whole && !chosen) t = fem_tuning{FEM_STRATEGY_LANE, 1, 4, 0};
     JacobianArgs a{n_elem, inv_j, det_j, coef, elem_mat};
     Launch l = make_launch(t, n_elem, 1, static_cast<hipStream_t>(stream));
     l.stream_out = whole;

@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <initializer_list>
 
 #include "fem.h"
@@ -60,20 +61,28 @@ struct Launch {
     int block;     // threads per workgroup (multiple of 64)
     int vec;       // elements per lane in load/store phases
     hipStream_t stream;
+    int max_grid = 1 << 22;  // workgroups that the configuration allows
     bool stream_out = true;  // output rows leave with streaming stores (row_st)
     int order = 0;           // place of each workgroup, RowOrder (row_block)
 };
 
+// Workgroups for one pass over so many lanes, and the grid: no more of them than
+// the configuration allows.
+inline int64_t blocks_for_lanes(const Launch& l, int64_t lanes) {
+    return std::max<int64_t>((lanes + l.block - 1) / l.block, 1);
+}
+inline int grid_for_lanes(const Launch& l, int64_t lanes) { return (int)std::min<int64_t>(blocks_for_lanes(l, lanes), l.max_grid); }
+
 // Workgroups that share a tile's element matrices, dealing out their `rows`
-// (columns, basis functions): as many as bring the launch to `want` waves, two
-// per SIMD. A wave writes its whole matrix in turn, so a small mesh waits for
+// (columns, basis functions): as many as bring the elements to `want` waves, two
+// per SIMD, within the workgroups that the configuration allows. A wave writes its whole matrix in turn, so a small mesh waits for
 // one wave: P3 matrices of 2926 tets, 3D elasticity FP32 452 us with 46 waves, 21
-// with 44 workgroups per tile; P3 mass FP64 31 and 6; P2 3D elasticity FP32 44
+// with 42 workgroups per tile; P3 mass FP64 31 and 6; P2 3D elasticity FP32 44
 // and 35. With 4096 waves wanted, most of the larger ones lose what the inputs
 // read again cost (P2 3D elasticity FP32, 40,007 tets 69 and 101 us).
-inline int matrix_parts(const Launch& l, int rows, int64_t want = 2048) {
-    const int64_t waves = (int64_t)l.grid * (l.block / 64);
-    const int64_t parts = want / (waves < 1 ? 1 : waves);
+inline int matrix_parts(const Launch& l, int64_t lanes, int rows, int64_t want = 2048) {
+    const int64_t blocks = blocks_for_lanes(l, lanes);
+    const int64_t parts = std::min<int64_t>(want / (blocks * (l.block / 64)), l.max_grid / std::min<int64_t>(blocks, l.max_grid));
     return parts < 1 ? 1 : parts > rows ? rows : (int)parts;
 }
 
@@ -171,8 +180,11 @@ fem_status hip_fail(hipError_t e, const char* what);
 // Compute units of the current device (cached per device); 0 if unknown.
 int device_cus();
 
-// Launch configuration table (fem_abi.hip), keyed by operation.
-fem_tuning get_tuning(int op, int dim, int phys, int rule, int dtype);
+// Launch configuration table (fem_abi.hip), keyed by operation. chosen: whether
+// the configuration was set, tuned or loaded (and is used as it is) or is the
+// built-in one.
+fem_tuning get_tuning(int op, int dim, int phys, int rule, int dtype, bool* chosen = nullptr);
+void drop_tuning(int op, int dim, int phys, int rule, int dtype);   // back to the built-in one
 void put_tuning(int op, int dim, int phys, int rule, int dtype, const fem_tuning& t);
 
 }  // namespace femq

@@ -384,15 +384,16 @@ static hipError_t launch_jac(int rule, int space, const JacobianArgs& a, const L
     };
     if constexpr (V > 1) {
         if (a.n >= (int64_t)V * 64 * (ELAST ? 1024 : 2048) && (ELAST || !l.stream_out)) {
-            m.grid = (l.grid + V - 1) / V;
-            const int parts = ELAST ? matrix_parts(m, LagBasis<DIM, ORDER>::NB) : 1;
+            const int64_t lanes = (a.n + V - 1) / V;
+            m.grid = grid_for_lanes(l, lanes);
+            const int parts = ELAST ? matrix_parts(l, lanes, LagBasis<DIM, ORDER>::NB) : 1;
             if constexpr (ELAST) {
                 if (l.stream_out) return go(jacobian_kernel<DIM, PHYS, ORDER, V, true, true, Real>, parts);
             }
             return go(jacobian_kernel<DIM, PHYS, ORDER, V, false, ELAST, Real>, parts);
         }
     }
-    const int parts = matrix_parts(l, LagBasis<DIM, ORDER>::NB);
+    const int parts = matrix_parts(l, a.n, LagBasis<DIM, ORDER>::NB);
     if (parts > 1) return go(jacobian_kernel<DIM, PHYS, ORDER, 1, false, true, Real>, parts);
     return l.stream_out ? go(jacobian_kernel<DIM, PHYS, ORDER, 1, true, false, Real>, 1)
                         : go(jacobian_kernel<DIM, PHYS, ORDER, 1, false, false, Real>, 1);

@@ -318,7 +318,7 @@ static hipError_t launch_jac(int space, const JacobianArgs& a, const Launch& l) 
     // the FP32 Laplacian is bound by its arithmetic and holds four waves per SIMD
     // (100,003 tets: 67 us with 2048 waves wanted, 53 with 4096); the others hold two
     const int64_t want = PHYS == FEM_LAPLACE && std::is_same<Real, float>::value ? 4096 : 2048;
-    hipLaunchKernelGGL(k, dim3(l.grid, matrix_parts(l, M, want)), dim3(l.block), 0, l.stream, a.n, l.order, space,
+    hipLaunchKernelGGL(k, dim3(l.grid, matrix_parts(l, a.n, M, want)), dim3(l.block), 0, l.stream, a.n, l.order, space,
                        static_cast<const Real*>(a.inv_j), static_cast<const Real*>(a.det_j),
                        static_cast<const Real*>(a.coef), static_cast<Real*>(a.out));
     return hipGetLastError();

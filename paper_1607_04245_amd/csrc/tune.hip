@@ -228,6 +228,8 @@ fem_status fem_autotune(int op, int dim, int physics, int rule, int dtype, int64
     fem_tuning current;
     fem_status st = fem_get_tuning(op, dim, physics, rule, dtype, &current);
     if (st) return st;
+    bool chosen = false;
+    (void)get_tuning(op, dim, physics, rule, dtype, &chosen);
     if (op == FEM_OP_GEOMETRY) physics = FEM_LAPLACE, rule = FEM_RULE_CENTROID;
     if (n_probe < 4096 || n_probe > (int64_t)1 << 28) {
         set_error("fem_autotune: n_elem_probe must be in [4096, 2^28]");
@@ -385,7 +387,8 @@ fem_status fem_autotune(int op, int dim, int physics, int rule, int dtype, int64
     (void)hipEventDestroy(t1);
     hipError_t sync = hipDeviceSynchronize();
     cleanup();
-    fem_set_tuning(op, dim, physics, rule, dtype, &best);
+    if (best_ms < 1e29f || chosen) fem_set_tuning(op, dim, physics, rule, dtype, &best);
+    else drop_tuning(op, dim, physics, rule, dtype);
     if (sync != hipSuccess) return hip_fail(sync, "fem_autotune");
     if (best_ms >= 1e29f) { set_error("fem_autotune: no candidate ran"); return FEM_ERR_HIP; }
 

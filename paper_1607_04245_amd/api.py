@@ -10,6 +10,7 @@ from __future__ import annotations
 import ctypes
 import functools
 import math
+import operator
 
 import torch
 
@@ -137,12 +138,16 @@ def fem_geometry(coords: torch.Tensor, conn: torch.Tensor, dtype=torch.float32, 
 
 @functools.lru_cache(maxsize=256)
 def _rows(dim, physics, rule, coef_space, order):
-    """Rows of (inv_j, closure) and the leading sizes of coef."""
+    """Rows of (inv_j, closure) and the leading sizes of coef; plain integers only."""
     return (dim * dim, n_basis(dim, order) * n_comp(dim, physics), n_coef(physics),
             n_coef_words(dim, rule, coef_space))
 
 
 def _shapes(dim, physics, rule, n, coef_space=N.COEF_QUAD, order=1):
+    # arrays and tensors of one element are integers here too (as in the C call),
+    # but cannot key a cache: they may change or have no hash
+    if not (type(dim) is type(physics) is type(rule) is type(coef_space) is type(order) is int):
+        dim, physics, rule, coef_space, order = map(operator.index, (dim, physics, rule, coef_space, order))
     ng, nbt, nm, nw = _rows(dim, physics, rule, coef_space, order)
     return (ng, n), (n,), (nbt, n), (nm, nw, n)
 

@@ -47,6 +47,11 @@ backward_p2_kernel(int64_t n, int order, const Real* __restrict__ inv_j, const R
         if (du != nullptr) {
             Real cf[E::NCQ], r[E::NBT];
             load_rows<E::NCQ>(coef, n, e, cf);
+            // all of them in flight before the arithmetic: without it the triangles'
+            // FP64 loads were issued one or two at a time to fit a fourth wave
+            // (elasticity, 811,008 triangles: 84 us, 79 with it); in 3D and in FP32
+            // it costs registers (3D elasticity FP32, 229,376 tets: 35 and 37)
+            if constexpr (DIM == 2 && sizeof(Real) == 8) __builtin_amdgcn_sched_barrier(0);
             element_residual_p2<DIM, PHYS, RULE, SPACE, Real>(ij, dj, ww, cf, r);
             store_rows<E::NBT, STREAM_OUT>(du, n, e, r);
         }

@@ -21,7 +21,7 @@ backward_lane_kernel(int64_t n, int order, const Real* __restrict__ inv_j, const
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     const bool want_du = du != nullptr;
     const bool want_dc = dcoef != nullptr;
-    for (int64_t ch = row_block(order) * blockDim.x + threadIdx.x; ch < nchunk; ch += stride) {
+    for (int64_t ch = row_block<STREAM_OUT>(order) * blockDim.x + threadIdx.x; ch < nchunk; ch += stride) {
         for_chunk<V>(ch * V, n, [&](auto width, int64_t e) {
             constexpr int W = decltype(width)::value;
             Real rij[E::NG][W], rdj[1][W], rw[E::NBT][W];

@@ -150,8 +150,11 @@ static TuneKey tune_key(int op, int dim, int phys, int rule, int dtype) {
 // middle choice. Where none was set or tuned, p1_tuning and the element
 // matrices refine them by count and alignment.
 static fem_tuning default_tuning(int op, int dim, int phys, int rule, int dtype) {
-    const fem_tuning t{FEM_STRATEGY_LANE, 1, 4, 0};  // RESIDUAL, BACKWARD: whole lines (p1_tuning)
     const bool f32 = dtype == FEM_F32;
+    // RESIDUAL, BACKWARD (whole lines; p1_tuning has odd words): four waves in FP32
+    // (two: 2 % slower at 100 to 460 MB), two in FP64 (four: 2D 2 % slower at 540 MB),
+    // one for scalar forms on FP64 tets (230 MB: 37.8 us, 41.0 with two)
+    const fem_tuning t{FEM_STRATEGY_LANE, 1, f32 ? 4 : dim == 3 && phys != FEM_ELASTICITY ? 1 : 2, 0};
     if (op == FEM_OP_GEOMETRY) return fem_tuning{FEM_STRATEGY_LANE, 4, 4, 0};
     if (op == FEM_OP_JACOBIAN || op == FEM_OP_JACOBIAN_P2) {  // store-bound: more waves for the larger P2 matrices
         if (phys == FEM_ELASTICITY) return op == FEM_OP_JACOBIAN_P2 ? fem_tuning{FEM_STRATEGY_LANE, 1, 4, 16} : fem_tuning{FEM_STRATEGY_LANE, 1, 1, 0};
@@ -163,10 +166,11 @@ static fem_tuning default_tuning(int op, int dim, int phys, int rule, int dtype)
     // lane kernel 238; FP64 571 and 471.)
     if (op == FEM_OP_RESIDUAL_P3 || op == FEM_OP_BACKWARD_P3) return fem_tuning{FEM_STRATEGY_LANE, 1, dim == 3 ? 1 : 4, 0};
     if (op == FEM_OP_JACOBIAN_P3) return fem_tuning{FEM_STRATEGY_LANE, 1, 4, 0};
-    // P2 (the remaining ops of one element per lane): FP32 streams best with
-    // four waves (2D elasticity, 2^22 triangles: 116 us with two, 110 with four),
-    // FP64 with one (3D elasticity adjoint, 1,000,001 tets: 270, 287 with two).
-    if (one_per_lane_op(op)) return fem_tuning{FEM_STRATEGY_LANE, 1, f32 ? 4 : 1, 0};
+    // P2 (the remaining ops of one element per lane): four waves (2D elasticity FP32,
+    // 2^22 triangles: 116 us with two, 110 with four; 2D FP64 at odd words, 620 MB: 4 %
+    // slower with two), one for FP64 tets (3D elasticity adjoint, 1,000,001 tets: 270,
+    // 287 with two; residuals and adjoints at 300 MB 8 % slower with four).
+    if (one_per_lane_op(op)) return fem_tuning{FEM_STRATEGY_LANE, 1, f32 || dim == 2 ? 4 : 1, 0};
     if (op == FEM_OP_RESIDUAL_GATHER) return fem_tuning{FEM_STRATEGY_LANE, 2, 1, 0};
     if (op == FEM_OP_RESIDUAL_MESH) {
         if (phys == FEM_LAPLACE && f32) return fem_tuning{FEM_STRATEGY_LANE, 1, 1, 8};
@@ -251,39 +255,50 @@ static int64_t row_words(int dim, int phys, int rule, int space, int order, int 
     return dim * dim + 1 + (int64_t)n_closure * nb * nc + (int64_t)n_coef_sets * m * nw;
 }
 
-// Stores and workgroup order of a launch over `bytes` of rows; whole: every
-// output row starts on a 128-byte line. One MI355X, us, bare rows or kernels:
-//  - Rows at odd words: plain stores, XCD by XCD. A line at a wave's edge is
-//    written in two parts; plain stores let the parts meet in the L2 that the
-//    neighbouring workgroups then share. 144 FP32 rows written: 1.8-2.4 TB/s
-//    streamed in launch order, 4.5 this way (whole lines 5.1-5.4); P2 3D
-//    elasticity FP32, 2,000,001 tets: 207 and 147.
-//  - Whole lines below 192 MiB, which the 256 MB last-level cache can hold:
-//    plain stores, runs of 16 workgroups per XCD. P1 3D Laplacian FP32, 2^20
-//    tets (92 MB): 16.4, and 18.2 XCD by XCD; P2 (172 MB): 29.7, and 32.1 as
-//    streamed in launch order.
-//  - Whole lines from 192 MiB up: XCD by XCD, each XCD streaming its own
-//    eighth of every row. P1 2D Laplacian FP64 (470 MB) 86 in launch order,
-//    75 this way; P1 3D elasticity FP64 (705 MB) 127 and 112.
-//  - and from 512 MB up with streaming stores: P1 3D elasticity FP64 112, 121
-//    plain; P2 3D elasticity FP32 (772 MB) 135, 146 plain; but at 352 MB (P1
-//    3D elasticity FP32) 59 streaming, 56 plain.
-static void set_rows(Launch& l, bool whole, int64_t bytes) {
-    l.stream_out = whole && bytes >= (int64_t)512 << 20;
-    l.order = !whole || bytes >= (int64_t)192 << 20 ? kOrderXcd : kOrderRuns;
+// Stores and workgroup order of a launch over `bytes` of rows of order-k elements;
+// whole: every output row starts on a 128-byte line. Runs: 16 consecutive workgroups
+// per XCD. One MI355X, inputs rotating through more than the last-level cache holds;
+// times relative to streaming stores in launch order unless said otherwise, means
+// over the Laplacian and elasticity, residual and adjoint.
+//  - Rows at odd words: plain stores in runs, so that the two parts of a line at a
+//    wave's edge meet in the L2 that neighbouring workgroups share: P1 FP32 0.82 at
+//    100 MB, 0.73 at 300, P2 FP32 0.72 and 0.67. (XCD by XCD 0.81 and 0.77 for P1, 1 %
+//    faster up to 100 MB, 2 to 7 % slower from 400 on, except on P3 tets: FP32, 200
+//    MB 0.63 and in runs 0.64, 900 MB 0.76 and 0.79.) P1 on FP64 triangles, where a
+//    wave's row has but two shared lines in five, streams from 544 MiB on (750 MB:
+//    0.96 of the first version's time, in runs 1.00; FP64 tets 0.80 and 0.79).
+//  - Whole lines that the 256 MB last-level cache can hold in part: plain stores in
+//    runs. Residuals: P1 0.97 at 130 to 300 MB, 0.99 at 450, 1.04 at 540; P2 0.97, 0.99
+//    (3D elasticity 1.08) and 1.05; P3 0.98, 1.05 and 1.07. Adjoints: P1 0.97, 0.95 and
+//    1.05, P2 0.97, 1.03 and 1.07, P3 0.97, 0.98 and 1.09. XCD by XCD, each XCD writing
+//    its own eighth of every row, is 3 % slower at 400 MB.
+//  - Whole lines above those limits, and below 64 MiB (128 on P3 tets), where plain
+//    stores push the inputs out (P3 tets, 60 MB: FP32 0.85 of the first version's time
+//    streamed, 0.91 plain; FP64 0.78 and 0.86): streaming stores in launch order. XCD by
+//    XCD they are 7 % slower at 700 MB.
+//  - `stream` asks for that at any size, where plain stores gain nothing: P3
+//    elasticity residuals, whose 20 or 60 rows leave in one burst after a long element
+//    (3D FP64, 230 MB: 33 us and 37; 2D: 43 and 48), and P1 residuals of scalar forms
+//    on FP64 tets, 4 rows out of 22 (230 MB: 37.8 and 39.0 us).
+static void set_rows(Launch& l, bool whole, int dim, int dtype, int64_t bytes, int order, bool adjoint, bool stream = false) {
+    const int64_t mib = bytes >> 20;
+    const int64_t low = order == 1 ? 0 : order == 3 && dim == 3 ? 128 : 64;
+    const int64_t high = !adjoint && (order == 1 || dim == 2) ? 448 : 416;
+    l.stream_out = whole ? stream || mib < low || mib >= high : order == 1 && dim == 2 && dtype == FEM_F64 && mib >= 544;
+    l.order = l.stream_out ? kOrderLaunch : !whole && order == 3 && dim == 3 ? kOrderXcd : kOrderRuns;
 }
 
-// Built-in configuration of the P1 lane kernels for n elements. Rows at odd words take
-// 16 bytes per lane (four FP32 or two FP64 elements), so that a wave shares 2
-// of its 9 lines with its neighbours and not 2 of 3 (FP32), as long as that
-// leaves two waves per SIMD: P1 3D Laplacian FP32, 1,500,001 tets, 25.1 us with
-// one element per lane, 23.0 with four (whole lines 23.4); its adjoint 34.4
-// and 31.0.
+// Built-in configuration of the P1 lane kernels for n elements. Rows at odd words
+// take four waves per workgroup, and from six waves of 16-byte lanes per SIMD on in
+// FP32 four elements per lane and one wave, so that a wave shares 2 of its 9 lines
+// with its neighbours and not 2 of 3: 3D Laplacian, 2,272,267 tets 36.8 us with one
+// element per lane, 35.0 with four, 3D elasticity, 1,784,843 tets 58.9 and 53.7; but
+// the adjoint of the 3D Laplacian on 735,243 tets 17.6 and 19.5. (FP64, where 16 bytes
+// are two elements: the same.)
 static fem_tuning p1_tuning(const fem_tuning& t, int dtype, int64_t n, bool whole) {
     if (whole) return t;
-    int vec = dtype == FEM_F32 ? 4 : 2;
-    while (vec > 1 && n < (int64_t)vec * 64 * 2048) vec >>= 1;
-    return fem_tuning{FEM_STRATEGY_LANE, vec, 1, 0};
+    if (dtype == FEM_F32 && n >= (int64_t)4 * 64 * 6144) return fem_tuning{FEM_STRATEGY_LANE, 4, 1, 0};
+    return fem_tuning{FEM_STRATEGY_LANE, 1, 4, 0};
 }
 
 static Launch make_launch(const fem_tuning& t, int64_t work_items, int vec, hipStream_t s) {
@@ -416,7 +431,8 @@ fem_status fem_integrate_residual(int dim, int physics, int rule, int coef_space
         const bool whole = whole_lines(n_elem, word, {elem_vec});
         if (!chosen) t = p1_tuning(t, dtype, n_elem, whole);
         Launch l = make_launch(t, (n_elem + t.vec - 1) / t.vec, t.vec, static_cast<hipStream_t>(stream));
-        set_rows(l, whole, n_elem * (int64_t)word * row_words(dim, physics, rule, coef_space, 1, 2, 1));
+        set_rows(l, whole, dim, dtype, n_elem * (int64_t)word * row_words(dim, physics, rule, coef_space, 1, 2, 1), 1, false,
+                 dim == 3 && dtype == FEM_F64 && physics != FEM_ELASTICITY);
         e = launch_residual_lane(dim, physics, rule, coef_space, dtype, a, l);
     }
     return e == hipSuccess ? FEM_OK : hip_fail(e, "fem_integrate_residual launch");
@@ -486,9 +502,9 @@ fem_status fem_integrate_residual_backward(int dim, int physics, int rule, int c
     if (!chosen) t = p1_tuning(t, dtype, n_elem, whole);
     BackwardArgs a{n_elem, inv_j, det_j, u, coef, w, du, dcoef};
     Launch l = make_launch(t, (n_elem + t.vec - 1) / t.vec, t.vec, static_cast<hipStream_t>(stream));
-    set_rows(l, whole, n_elem * (int64_t)word *
+    set_rows(l, whole, dim, dtype, n_elem * (int64_t)word *
                            row_words(dim, physics, rule, coef_space, 1, (du ? 2 : 1) + (dcoef ? 1 : 0),
-                                     (du ? 1 : 0) + (dcoef ? 1 : 0)));
+                                     (du ? 1 : 0) + (dcoef ? 1 : 0)), 1, true);
     hipError_t e = launch_backward_lane(dim, physics, rule, coef_space, dtype, a, l);
     return e == hipSuccess ? FEM_OK : hip_fail(e, "fem_integrate_residual_backward launch");
 }
@@ -509,8 +525,8 @@ fem_status fem_integrate_residual_p2(int dim, int physics, int rule, int coef_sp
     ResidualArgs a{n_elem, inv_j, det_j, u, coef, elem_vec};
     Launch l = make_launch(t, n_elem, 1, static_cast<hipStream_t>(stream));
     const size_t word = dtype == FEM_F32 ? 4 : 8;
-    set_rows(l, whole_lines(n_elem, word, {elem_vec}),
-             n_elem * (int64_t)word * row_words(dim, physics, rule, coef_space, 2, 2, 1));
+    set_rows(l, whole_lines(n_elem, word, {elem_vec}), dim, dtype,
+             n_elem * (int64_t)word * row_words(dim, physics, rule, coef_space, 2, 2, 1), 2, false);
     hipError_t e = launch_residual_p2(dim, physics, rule, coef_space, dtype, a, l);
     return e == hipSuccess ? FEM_OK : hip_fail(e, "fem_integrate_residual_p2 launch");
 }
@@ -544,8 +560,8 @@ fem_status fem_integrate_residual_p3(int dim, int physics, int rule, int coef_sp
     } else {
         Launch l = make_launch(t, n_elem, 1, static_cast<hipStream_t>(stream));
         const size_t word = dtype == FEM_F32 ? 4 : 8;
-        set_rows(l, whole_lines(n_elem, word, {elem_vec}),
-                 n_elem * (int64_t)word * row_words(dim, physics, rule, coef_space, 3, 2, 1));
+        set_rows(l, whole_lines(n_elem, word, {elem_vec}), dim, dtype,
+                 n_elem * (int64_t)word * row_words(dim, physics, rule, coef_space, 3, 2, 1), 3, false, physics == FEM_ELASTICITY);
         e = launch_residual_p3(dim, physics, coef_space, dtype, a, l);
     }
     return e == hipSuccess ? FEM_OK : hip_fail(e, "fem_integrate_residual_p3 launch");
@@ -567,8 +583,8 @@ fem_status fem_integrate_residual_p2_backward(int dim, int physics, int rule, in
     BackwardArgs a{n_elem, inv_j, det_j, u, coef, w, du, dcoef};
     Launch l = make_launch(t, n_elem, 1, static_cast<hipStream_t>(stream));
     const size_t word = dtype == FEM_F32 ? 4 : 8;
-    set_rows(l, whole_lines(n_elem, word, {du, dcoef}),
-             n_elem * (int64_t)word * row_words(dim, physics, rule, coef_space, 2, (du ? 2 : 1) + (dcoef ? 1 : 0), (du ? 1 : 0) + (dcoef ? 1 : 0)));
+    set_rows(l, whole_lines(n_elem, word, {du, dcoef}), dim, dtype,
+             n_elem * (int64_t)word * row_words(dim, physics, rule, coef_space, 2, (du ? 2 : 1) + (dcoef ? 1 : 0), (du ? 1 : 0) + (dcoef ? 1 : 0)), 2, true);
     hipError_t e = launch_backward_p2(dim, physics, rule, coef_space, dtype, a, l);
     return e == hipSuccess ? FEM_OK : hip_fail(e, "fem_integrate_residual_p2_backward launch");
 }
@@ -589,8 +605,8 @@ fem_status fem_integrate_residual_p3_backward(int dim, int physics, int rule, in
     BackwardArgs a{n_elem, inv_j, det_j, u, coef, w, du, dcoef};
     Launch l = make_launch(t, n_elem, 1, static_cast<hipStream_t>(stream));
     const size_t word = dtype == FEM_F32 ? 4 : 8;
-    set_rows(l, whole_lines(n_elem, word, {du, dcoef}),
-             n_elem * (int64_t)word * row_words(dim, physics, rule, coef_space, 3, (du ? 2 : 1) + (dcoef ? 1 : 0), (du ? 1 : 0) + (dcoef ? 1 : 0)));
+    set_rows(l, whole_lines(n_elem, word, {du, dcoef}), dim, dtype,
+             n_elem * (int64_t)word * row_words(dim, physics, rule, coef_space, 3, (du ? 2 : 1) + (dcoef ? 1 : 0), (du ? 1 : 0) + (dcoef ? 1 : 0)), 3, true);
     hipError_t e = launch_backward_p3(dim, physics, coef_space, dtype, a, l);
     return e == hipSuccess ? FEM_OK : hip_fail(e, "fem_integrate_residual_p3_backward launch");
 }

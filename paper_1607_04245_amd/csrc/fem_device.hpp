@@ -477,11 +477,11 @@ __device__ __forceinline__ void geometry_finish(bool valid, int64_t e, int64_t n
 // L2 instead of spilling to the shared last-level cache.
 constexpr int kXcds = 8;
 
-__device__ __forceinline__ int64_t xcd_logical_block(int64_t b, int64_t g) {
-    const int64_t per = (g + kXcds - 1) / kXcds;  // logical blocks of the fuller XCDs
-    const int64_t rem = g % kXcds;                // XCDs holding `per` blocks (all, if 0)
-    const int64_t xcd = b % kXcds, slot = b / kXcds;
-    const int64_t start = (rem == 0 || xcd < rem) ? xcd * per : rem * per + (xcd - rem) * (per - 1);
+__device__ __forceinline__ int64_t xcd_logical_block(uint32_t b, uint32_t g) {
+    const uint32_t per = (g + kXcds - 1) / kXcds;  // logical blocks of the fuller XCDs
+    const uint32_t rem = g % kXcds;                // XCDs holding `per` blocks (all, if 0)
+    const uint32_t xcd = b % kXcds, slot = b / kXcds;
+    const uint32_t start = (rem == 0 || xcd < rem) ? xcd * per : rem * per + (xcd - rem) * (per - 1);
     return start + slot;
 }
 
@@ -497,11 +497,21 @@ __device__ __forceinline__ void block_tile_range(int64_t n_tiles, int64_t& begin
 // number, numbered XCD by XCD, or with runs of kRun consecutive places dealt
 // to the XCDs in turn.
 __device__ __forceinline__ int64_t row_block(int order) {
-    if (order == kOrderXcd) return xcd_logical_block(blockIdx.x, gridDim.x);
-    const int64_t b = blockIdx.x;
-    constexpr int64_t span = kXcds * kRun;
-    if (order == kOrderLaunch || b >= gridDim.x / span * span) return b;
-    return b / span * span + b % kXcds * kRun + b % span / kXcds;
+    const uint32_t b = blockIdx.x;
+    if (order == kOrderLaunch) return b;
+    if (order == kOrderXcd) return xcd_logical_block(b, gridDim.x);
+    constexpr uint32_t span = kXcds * kRun;
+    return b >= gridDim.x / span * span ? b : b / span * span + b % kXcds * kRun + b % span / kXcds;
+}
+
+// The same for a kernel whose stores stream or not: streaming launches are in
+// launch order, known at compile time. (With the order as an argument a wave
+// waits for two more scalar loads before its first row: P1 3D Laplacian matrices
+// FP64 of 163,840 tets 9.2 us, 8.6 without.)
+template <bool STREAM_OUT>
+__device__ __forceinline__ int64_t row_block(int order) {
+    if constexpr (STREAM_OUT) return blockIdx.x;
+    else return row_block(order);
 }
 
 // Words e of N consecutive rows.

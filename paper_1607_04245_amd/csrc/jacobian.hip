@@ -287,7 +287,7 @@ jacobian_kernel(int64_t n, int order, int rule, int space, const Real* __restric
     constexpr int NCOEF = PHYS == FEM_ELASTICITY ? 2 : 1;
     const int64_t nchunk = (n + V - 1) / V;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t ch = row_block(order) * blockDim.x + threadIdx.x; ch < nchunk; ch += stride) {
+    for (int64_t ch = (V == 1 ? row_block<STREAM_OUT>(order) : row_block(order)) * blockDim.x + threadIdx.x; ch < nchunk; ch += stride) {
         for_chunk<V>(ch * V, n, [&](auto width, int64_t e) {
             constexpr int W = decltype(width)::value;
             Real dj[1][W];

@@ -76,7 +76,7 @@ residual_planned_kernel(int64_t n, int64_t n_tiles, const int64_t* __restrict__ 
     Real* vs = reinterpret_cast<Real*>(plan_lds + (int64_t)TPW * maxc * DIM);
     const int lane = threadIdx.x;
     int ndeg = 0, npoor = 0;
-    for (int64_t t0 = row_block(order) * TPW; t0 < n_tiles; t0 += (int64_t)gridDim.x * TPW) {
+    for (int64_t t0 = row_block<STREAM_OUT>(order) * TPW; t0 < n_tiles; t0 += (int64_t)gridDim.x * TPW) {
         int64_t off[TPW], e[TPW];
         int cnt[TPW];
         uint32_t li[TPW];
@@ -161,7 +161,7 @@ geometry_planned_kernel(int64_t n, int64_t n_tiles, const int64_t* __restrict__ 
     extern __shared__ double plan_lds[];
     const int lane = threadIdx.x;
     int ndeg = 0, npoor = 0;
-    for (int64_t t = row_block(order); t < n_tiles; t += gridDim.x) {
+    for (int64_t t = row_block<STREAM_OUT>(order); t < n_tiles; t += gridDim.x) {
         const int64_t off = tile_off[t];
         const int cnt = (int)(tile_off[t + 1] - off);
         const int64_t e = t * kPlanTile + lane, ec = e < n ? e : n - 1;

@@ -3,11 +3,11 @@
 // Each lane owns V consecutive elements. Every structure-of-arrays row is
 // read with one V-wide vector load per lane, so a wavefront reads 64*V
 // consecutive words of a row at once (fully coalesced). Rows may start on any
-// word: the rows of an odd element count do, and V = 4 (FP32) or 2 (FP64) is
-// there for them, since a wave then shares only the two lines at the ends of
-// its 1 KB with other waves (P1 3D Laplacian FP32, 1,500,001 tets: 31.5 us
-// with one element per lane and streaming stores, 23-26 us with four and
-// plain stores, floor 20.5 us). The quadrature phase (pointwise f0/f1 at every
+// word: the rows of an odd element count do, and V = 4 is there for them in FP32,
+// since a wave then shares only the two lines at the ends of its 1 KB with other
+// waves (P1 3D Laplacian FP32, 2,272,267 tets: 50.4 us with one element per lane and
+// streaming stores, 36.8 with plain stores in runs of workgroups, 35.0 with four
+// elements per lane, floor 31.0). The quadrature phase (pointwise f0/f1 at every
 // point) and the basis phase (sum back onto the basis functions) run in
 // registers, so no value crosses lanes and no reduction is needed; the paper's
 // concern about per-thread storage (Section 1) does not bind on gfx950, whose
@@ -25,7 +25,7 @@ residual_lane_kernel(int64_t n, int order, const Real* __restrict__ inv_j, const
     using E = Elem<DIM, PHYS, RULE>;
     const int64_t nchunk = (n + V - 1) / V;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t ch = row_block(order) * blockDim.x + threadIdx.x; ch < nchunk; ch += stride) {
+    for (int64_t ch = row_block<STREAM_OUT>(order) * blockDim.x + threadIdx.x; ch < nchunk; ch += stride) {
         for_chunk<V>(ch * V, n, [&](auto width, int64_t e) {
             constexpr int W = decltype(width)::value;
             Real rij[E::NG][W], rdj[1][W], ru[E::NBT][W], rcf[E::NCQ][W], rr[E::NBT][W];

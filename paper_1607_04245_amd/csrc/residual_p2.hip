@@ -19,7 +19,7 @@ residual_p2_kernel(int64_t n, int order, const Real* __restrict__ inv_j, const R
                    const Real* __restrict__ u, const Real* __restrict__ coef, Real* __restrict__ out) {
     using E = ElemP2<DIM, PHYS, RULE, SPACE>;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t e = row_block(order) * blockDim.x + threadIdx.x; e < n; e += stride) {
+    for (int64_t e = row_block<STREAM_OUT>(order) * blockDim.x + threadIdx.x; e < n; e += stride) {
         Real ij[E::NG], uu[E::NBT], cf[E::NCQ], r[E::NBT];
         load_rows<E::NG>(inv_j, n, e, ij);
         const Real dj = row_ld(det_j + e);
@@ -39,7 +39,7 @@ backward_p2_kernel(int64_t n, int order, const Real* __restrict__ inv_j, const R
                    Real* __restrict__ du, Real* __restrict__ dcoef) {
     using E = ElemP2<DIM, PHYS, RULE, SPACE>;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t e = row_block(order) * blockDim.x + threadIdx.x; e < n; e += stride) {
+    for (int64_t e = row_block<STREAM_OUT>(order) * blockDim.x + threadIdx.x; e < n; e += stride) {
         Real ij[E::NG], ww[E::NBT];
         load_rows<E::NG>(inv_j, n, e, ij);
         const Real dj = row_ld(det_j + e);

@@ -76,9 +76,8 @@ residual_p3_kernel(int64_t n, int order, int space, const Real* __restrict__ inv
                    const Real* __restrict__ u, const Real* __restrict__ coef, Real* __restrict__ out) {
     constexpr int RULE = DIM == 2 ? FEM_RULE_TRI6 : FEM_RULE_TET11;
     using E = ElemP3<DIM, PHYS, RULE, FEM_COEF_QUAD>;
-    using Q = RuleP2<DIM, RULE>;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t e = row_block(order) * blockDim.x + threadIdx.x; e < n; e += stride) {
+    for (int64_t e = row_block<STREAM_OUT>(order) * blockDim.x + threadIdx.x; e < n; e += stride) {
         Real ij[E::NG], uu[E::NBT], aq[E::NCQ];
         load_rows<E::NG>(inv_j, n, e, ij);
         const Real dj = row_ld(det_j + e);
@@ -111,7 +110,7 @@ backward_p3_kernel(int64_t n, int order, int space, const Real* __restrict__ inv
     using E = ElemP3<DIM, PHYS, RULE, FEM_COEF_QUAD>;
     using Q = RuleP2<DIM, RULE>;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t e = row_block(order) * blockDim.x + threadIdx.x; e < n; e += stride) {
+    for (int64_t e = row_block<STREAM_OUT>(order) * blockDim.x + threadIdx.x; e < n; e += stride) {
         Real ij[E::NG], ww[E::NBT];
         load_rows<E::NG>(inv_j, n, e, ij);
         const Real dj = row_ld(det_j + e);
@@ -228,7 +227,7 @@ jacobian_p3_kernel(int64_t n, int order, int space, const Real* __restrict__ inv
     constexpr int M = E::NBT, NC = E::NC, NV = E::NV, NB = E::NB;
     const auto& tab = p3_table<DIM>();
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t e = row_block(order) * blockDim.x + threadIdx.x; e < n; e += stride) {
+    for (int64_t e = row_block<STREAM_OUT>(order) * blockDim.x + threadIdx.x; e < n; e += stride) {
         Real ij[E::NG], aq[E::NCQ];
         load_rows<E::NG>(inv_j, n, e, ij);
         const Real adj = fabs(row_ld(det_j + e));

@@ -45,14 +45,16 @@ def _lanes(n, vec):
 # a chosen configuration with the built-in one's values is used as it is, at odd
 # words too, where the built-in one is refined
 @pytest.mark.parametrize("call,op", [("residual", N.OP_RESIDUAL), ("backward", N.OP_BACKWARD)])
-@pytest.mark.parametrize("dtype,wide", [(F32, 4), (F64, 2)])
-@pytest.mark.parametrize("n,offset", [(1000001, 0), (1 << 20, 1)])
-def test_chosen_shape_at_odd_words(launches, call, op, dtype, wide, n, offset):
+@pytest.mark.parametrize("dtype,waves,odd", [(F32, 4, (4, 1)), (F64, 1, (1, 4))])
+@pytest.mark.parametrize("n,offset", [((1 << 21) + 1, 0), (1 << 21, 1)])
+def test_chosen_shape_at_odd_words(launches, call, op, dtype, waves, odd, n, offset):
     key = (3, mg.LAPLACE, mg.RULE_TET4)
     c = (call, *key, N.COEF_QUAD, dtype, n, offset)
-    built_in, chosen = launches(c, ("set", op, *key, dtype, N.STRATEGY_LANE, 1, 4, 0), c)
-    assert built_in["args"][4] == str(wide) and built_in["block"] == 64
-    assert chosen["args"][4] == "1" and chosen["block"] == 256 and chosen["grid"] == (_lanes(n, 256), 1)
+    whole, built_in, chosen = launches((call, *key, N.COEF_QUAD, dtype, 1 << 21, 0), c,
+                                       ("set", op, *key, dtype, N.STRATEGY_LANE, 1, waves, 0), c)
+    assert (whole["args"][4], whole["block"]) == ("1", 64 * waves)
+    assert (built_in["args"][4], built_in["block"]) == (str(odd[0]), 64 * odd[1])
+    assert (chosen["args"][4], chosen["block"]) == ("1", 64 * waves) and chosen["grid"] == (_lanes(n, 64 * waves), 1)
 
 
 @pytest.mark.parametrize("order,op,rule", [(1, N.OP_JACOBIAN, mg.RULE_TET4), (2, N.OP_JACOBIAN_P2, mg.RULE_TET11),
@@ -81,3 +83,17 @@ def test_built_in_matrix_shapes(launches):
     key = (3, mg.ELASTICITY, mg.RULE_TET11)
     small, large = launches(("jacobian", *key, N.COEF_QUAD, F32, 2926, 0, 3), ("jacobian", *key, N.COEF_QUAD, F32, 131072, 0, 3))
     assert small["grid"] == (12, 42) and large["grid"] == (512, 1)
+
+
+# rows at whole lines: plain stores in runs of workgroups where the last-level cache
+# can hold some of them, streaming stores in launch order above; at odd words plain
+# stores in runs, but FP64 triangles stream when large
+@pytest.mark.parametrize("dim,physics,dtype,n,offset,stream", [
+    (3, mg.ELASTICITY, F32, 1 << 20, 0, 0), (3, mg.ELASTICITY, F32, 2796160, 0, 0), (3, mg.ELASTICITY, F32, 2796224, 0, 1),
+    (3, mg.LAPLACE, F64, 1 << 20, 0, 1), (2, mg.LAPLACE, F64, (1 << 22) - 32, 0, 0), (3, mg.ELASTICITY, F32, 2796224, 1, 0),
+    (3, mg.ELASTICITY, F64, 1 << 21, 1, 0), (2, mg.ELASTICITY, F64, 1 << 21, 1, 0), (2, mg.ELASTICITY, F64, 3100000, 1, 0),
+    (2, mg.ELASTICITY, F64, 3100704, 1, 1)])
+def test_row_stores(launches, dim, physics, dtype, n, offset, stream):
+    rule = mg.RULE_TRI3 if dim == 2 else mg.RULE_TET4
+    got, = launches(("residual", dim, physics, rule, N.COEF_QUAD, dtype, n, offset))
+    assert got["args"][5] == ("true" if stream else "false") and got["order"] == (0 if stream else 2)

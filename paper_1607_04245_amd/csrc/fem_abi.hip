@@ -156,10 +156,12 @@ static fem_tuning default_tuning(int op, int dim, int phys, int rule, int dtype)
     // one for scalar forms on FP64 tets (230 MB: 37.8 us, 41.0 with two)
     const fem_tuning t{FEM_STRATEGY_LANE, 1, f32 ? 4 : dim == 3 && phys != FEM_ELASTICITY ? 1 : 2, 0};
     if (op == FEM_OP_GEOMETRY) return fem_tuning{FEM_STRATEGY_LANE, 4, 4, 0};
-    if (op == FEM_OP_JACOBIAN || op == FEM_OP_JACOBIAN_P2) {  // store-bound: more waves for the larger P2 matrices
-        if (phys == FEM_ELASTICITY) return op == FEM_OP_JACOBIAN_P2 ? fem_tuning{FEM_STRATEGY_LANE, 1, 4, 16} : fem_tuning{FEM_STRATEGY_LANE, 1, 1, 0};
-        return op == FEM_OP_JACOBIAN_P2 ? fem_tuning{FEM_STRATEGY_LANE, 1, 4, 0} : fem_tuning{FEM_STRATEGY_LANE, 1, 2, 0};
-    }
+    // Store-bound. FP64 scalar matrices stream best with one wave (P2 3D Laplacian,
+    // 30,720 tets 9.4 us, 10.5 with four; P1 245,760 tets 12.0, 13.1 with two), the
+    // larger P2 elements with four (3D elasticity FP64, 40,960 tets 80 us, 84 with one;
+    // 3D Laplacian FP32, 491,520 tets 55 and 59).
+    if (op == FEM_OP_JACOBIAN_P2) return fem_tuning{FEM_STRATEGY_LANE, 1, f32 || phys == FEM_ELASTICITY ? 4 : 1, phys == FEM_ELASTICITY ? 16 : 0};
+    if (op == FEM_OP_JACOBIAN) return fem_tuning{FEM_STRATEGY_LANE, 1, f32 && phys != FEM_ELASTICITY ? 2 : 1, 0};
     // P3: the 3D elements hold 20-60 closure and output words per lane, and
     // single-wave workgroups measured fastest there; 2D streams better with
     // four. (The component split of 3D elasticity, 2^21 tets: FP32 271 us, the
@@ -629,13 +631,18 @@ fem_status fem_integrate_jacobian(int dim, int physics, int rule, int coef_space
     // Rows at odd words: four waves per workgroup, XCD by XCD. Whole lines in
     // launch order (P1 3D elasticity FP64, one element per lane: 400,000 tets 113
     // us, 115 us XCD by XCD; 400,001 tets 184 us streaming in launch order, 145
-    // us this way).
-    const bool whole = whole_lines(n_elem, dtype == FEM_F32 ? 4 : 8, {elem_mat});
-    if (!whole && !chosen) t = fem_tuning{FEM_STRATEGY_LANE, 1, 4, 0};
+    // us this way), but P1 elasticity rows of 4 MiB or more, whose kernels give a
+    // lane 16 bytes of a row, four waves and XCD by XCD as well: 3D FP64, 327,680
+    // tets 86 us, 88 this way, 524,288 tets 138 and 135, 2^21 tets 569 and 544; 2D
+    // FP32, 2^21 triangles 81 and 77.
+    const size_t word = dtype == FEM_F32 ? 4 : 8;
+    const bool whole = whole_lines(n_elem, word, {elem_mat});
+    const bool by_xcd = !whole || (order == 1 && physics == FEM_ELASTICITY && n_elem * (int64_t)word >= (int64_t)4 << 20);
+    if (by_xcd && !chosen) t = fem_tuning{FEM_STRATEGY_LANE, 1, 4, 0};
     JacobianArgs a{n_elem, inv_j, det_j, coef, elem_mat};
     Launch l = make_launch(t, n_elem, 1, static_cast<hipStream_t>(stream));
     l.stream_out = whole;
-    l.order = whole ? kOrderLaunch : kOrderXcd;
+    l.order = by_xcd ? kOrderXcd : kOrderLaunch;
     hipError_t e = order == 3 ? launch_jacobian_p3(dim, physics, coef_space, dtype, a, l)
                               : launch_jacobian(dim, physics, order, rule, coef_space, dtype, a, l);
     return e == hipSuccess ? FEM_OK : hip_fail(e, "fem_integrate_jacobian launch");

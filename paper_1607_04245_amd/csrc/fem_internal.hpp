@@ -74,17 +74,20 @@ inline int64_t blocks_for_lanes(const Launch& l, int64_t lanes) {
 inline int grid_for_lanes(const Launch& l, int64_t lanes) { return (int)std::min<int64_t>(blocks_for_lanes(l, lanes), l.max_grid); }
 
 // Workgroups that share a tile's element matrices, dealing out their `rows`
-// (columns, basis functions): as many as bring the elements to `want` waves, two
-// per SIMD, within the workgroups that the configuration allows. A wave writes its whole matrix in turn, so a small mesh waits for
-// one wave: P3 matrices of 2926 tets, 3D elasticity FP32 452 us with 46 waves, 21
-// with 42 workgroups per tile; P3 mass FP64 31 and 6; P2 3D elasticity FP32 44
-// and 35. With 4096 waves wanted, most of the larger ones lose what the inputs
-// read again cost (P2 3D elasticity FP32, 40,007 tets 69 and 101 us).
-inline int matrix_parts(const Launch& l, int64_t lanes, int rows, int64_t want = 2048) {
-    const int64_t blocks = blocks_for_lanes(l, lanes);
-    const int64_t parts = std::min<int64_t>(want / (blocks * (l.block / 64)), l.max_grid / std::min<int64_t>(blocks, l.max_grid));
+// (columns, basis functions): as many as bring the elements to `want` waves
+// within the workgroups that the configuration allows. A wave writes its whole
+// matrix in turn, so a small mesh waits for one wave: P3 matrices of 2926 tets, 3D
+// elasticity FP32 452 us with 46 waves, 21 with 42 workgroups per tile. Each share
+// reads the inputs again and, for P1 and P2, forms the moments again, so these want
+// no more than 640 waves: P2 3D elasticity FP64, whole lines, 4096 tets 54 us
+// unshared, 37 among ten; 10,240 tets 55, 42 among four, 71 among ten; 40,960 tets
+// 82, 112 among three.
+inline int matrix_parts(const Launch& l, int64_t lanes, int rows, int64_t want) {
+    const int64_t blocks = blocks_for_lanes(l, lanes), waves = blocks * (l.block / 64);
+    const int64_t parts = std::min<int64_t>(want / waves, l.max_grid / std::min<int64_t>(blocks, l.max_grid));
     return parts < 1 ? 1 : parts > rows ? rows : (int)parts;
 }
+constexpr int64_t kMatrixWaves = 640;   // P1 and P2
 
 // Whether rows of n words in each of the given arrays (NULL ones are skipped)
 // all start on a 128-byte cache line.

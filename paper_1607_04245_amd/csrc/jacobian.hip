@@ -363,10 +363,11 @@ jacobian_kernel(int64_t n, int order, int rule, int space, const Real* __restric
 
 // Elements per lane, V: 16 bytes of every row for P1, where the matrices are
 // short enough for V sets of moments and gradients in the registers.
-//  - Elasticity, as long as that leaves a wave per SIMD. Odd words, four waves
-//    per workgroup: 3D FP32, 1,000,001 tets 190 us with V = 1, 159 with 4;
-//    FP64, 200,001 tets 75 and 64. Whole lines: 3D FP32, 400,000 tets 61 and
-//    54; FP64 112 and 107 (518 MB, 4.8 TB/s).
+//  - Elasticity, as long as that leaves a wave per SIMD, in FP32 at odd words two.
+//    Odd words, four waves per workgroup: 3D FP32, 327,691 tets 63 us with V = 1,
+//    69 with 4, 524,309 tets 101 and 80; FP64, 163,859 tets 57 and 56, 2^20 + 3 tets
+//    354 and 342. Whole lines: 3D FP32, 327,680 tets 50 and 46; FP64, 400,000 tets
+//    112 and 107 (518 MB, 4.8 TB/s).
 //  - Laplacian and mass FP32 at odd words, as long as that leaves two: 3D,
 //    1,000,001 tets 26.8 and 24.4 us, mass 20.4 and 18.3; but 300,001 tets 9.2
 //    and 11.2. Whole lines lose (FP64, 2^20 tets 46 and 52), FP64 at odd words
@@ -383,18 +384,18 @@ static hipError_t launch_jac(int rule, int space, const JacobianArgs& a, const L
         return hipGetLastError();
     };
     if constexpr (V > 1) {
-        if (a.n >= (int64_t)V * 64 * (ELAST ? 1024 : 2048) && (ELAST || !l.stream_out)) {
-            const int64_t lanes = (a.n + V - 1) / V;
-            m.grid = grid_for_lanes(l, lanes);
-            const int parts = ELAST ? matrix_parts(l, lanes, LagBasis<DIM, ORDER>::NB) : 1;
+        const int64_t waves = ELAST && (l.stream_out || sizeof(Real) == 8) ? 1024 : 2048;
+        if (a.n >= V * 64 * waves && (ELAST || !l.stream_out)) {
+            m.grid = grid_for_lanes(l, (a.n + V - 1) / V);
             if constexpr (ELAST) {
-                if (l.stream_out) return go(jacobian_kernel<DIM, PHYS, ORDER, V, true, true, Real>, parts);
+                if (l.stream_out) return go(jacobian_kernel<DIM, PHYS, ORDER, V, true, true, Real>, 1);
             }
-            return go(jacobian_kernel<DIM, PHYS, ORDER, V, false, ELAST, Real>, parts);
+            return go(jacobian_kernel<DIM, PHYS, ORDER, V, false, ELAST, Real>, 1);
         }
     }
-    const int parts = matrix_parts(l, a.n, LagBasis<DIM, ORDER>::NB);
-    if (parts > 1) return go(jacobian_kernel<DIM, PHYS, ORDER, 1, false, true, Real>, parts);
+    const int parts = matrix_parts(l, a.n, LagBasis<DIM, ORDER>::NB, kMatrixWaves);
+    if (parts > 1) return l.stream_out ? go(jacobian_kernel<DIM, PHYS, ORDER, 1, true, true, Real>, parts)
+                                       : go(jacobian_kernel<DIM, PHYS, ORDER, 1, false, true, Real>, parts);
     return l.stream_out ? go(jacobian_kernel<DIM, PHYS, ORDER, 1, true, false, Real>, 1)
                         : go(jacobian_kernel<DIM, PHYS, ORDER, 1, false, false, Real>, 1);
 }

@@ -314,9 +314,16 @@ template <int DIM, int PHYS, typename Real>
 static hipError_t launch_jac(int space, const JacobianArgs& a, const Launch& l) {
     constexpr int M = ElemP3<DIM, PHYS, DIM == 2 ? FEM_RULE_TRI6 : FEM_RULE_TET11, FEM_COEF_QUAD>::NBT;
     const auto k = l.stream_out ? jacobian_p3_kernel<DIM, PHYS, Real, true> : jacobian_p3_kernel<DIM, PHYS, Real, false>;
-    // the FP32 Laplacian is bound by its arithmetic and holds four waves per SIMD
-    // (100,003 tets: 67 us with 2048 waves wanted, 53 with 4096); the others hold two
-    const int64_t want = PHYS == FEM_LAPLACE && std::is_same<Real, float>::value ? 4096 : 2048;
+    // Two waves per SIMD, which is what the registers hold; the FP32 Laplacian is
+    // bound by its arithmetic and holds four (100,003 tets: 67 us with 2048 waves
+    // wanted, 53 with 4096). No more than that many, so that all shares run at once (3D
+    // elasticity FP32, 10,240 tets: 40 us with 12, 57 with 13), but whole lines of up to
+    // two thirds as many waves take two shares (2D elasticity FP32, 81,920 triangles 37
+    // and 30 us, 3D mass FP32 33 and 30; at odd words that loses: 3D Laplacian FP32,
+    // 163,859 tets 77 and 83).
+    int64_t want = PHYS == FEM_LAPLACE && std::is_same<Real, float>::value ? 4096 : 2048;
+    const int64_t waves = blocks_for_lanes(l, a.n) * (l.block / 64);
+    if (l.stream_out && 2 * waves > want && 3 * waves <= 2 * want) want = 2 * waves;
     hipLaunchKernelGGL(k, dim3(l.grid, matrix_parts(l, a.n, M, want)), dim3(l.block), 0, l.stream, a.n, l.order, space,
                        static_cast<const Real*>(a.inv_j), static_cast<const Real*>(a.det_j),
                        static_cast<const Real*>(a.coef), static_cast<Real*>(a.out));

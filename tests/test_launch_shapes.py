@@ -97,3 +97,13 @@ def test_row_stores(launches, dim, physics, dtype, n, offset, stream):
     rule = mg.RULE_TRI3 if dim == 2 else mg.RULE_TET4
     got, = launches(("residual", dim, physics, rule, N.COEF_QUAD, dtype, n, offset))
     assert got["args"][5] == ("true" if stream else "false") and got["order"] == (0 if stream else 2)
+
+
+# shares of a tile's P1 and P2 matrices: no more than 640 waves, streaming at whole
+# lines; one share from 640 waves of elements on
+@pytest.mark.parametrize("n,share", [(1024, 10), (4096, 10), (10240, 4), (10243, 3), (20480, 2), (40960, 1), (163840, 1)])
+@pytest.mark.parametrize("dtype", [F32, F64])
+def test_matrix_shares(launches, dtype, n, share):
+    got, = launches(("jacobian", 3, mg.ELASTICITY, mg.RULE_TET11, N.COEF_QUAD, dtype, n, 0, 2))
+    assert got["grid"] == (_lanes(n, 256), share)
+    assert got["args"][4] == ("true" if n % 32 == 0 else "false")

@@ -35,6 +35,7 @@ OP_JACOBIAN, OP_JACOBIAN_P2 = 7, 8
 OP_RESIDUAL_P3, OP_BACKWARD_P3, OP_JACOBIAN_P3 = 9, 10, 11
 COEF_QUAD, COEF_P1, COEF_P0 = 0, 1, 2
 BATCH_NOALLOC_MAX_MESHES = 1024
+BATCH_WAVES, BATCH_BLOCKS_PER_CU = 4, 0   # the launch shape a batch plan starts with
 
 
 class FemError(RuntimeError):

@@ -474,7 +474,8 @@ def _mesh_descs(meshes: list[dict]):
     return descs, dtype
 
 
-def batch_run_noalloc(meshes: list[dict], waves_per_block: int = 8, blocks_per_cu: int = 0):
+def batch_run_noalloc(meshes: list[dict], waves_per_block: int = N.BATCH_WAVES,
+                      blocks_per_cu: int = N.BATCH_BLOCKS_PER_CU):
     """The batched launch without a plan and without any device allocation
     (fem_batch_run_noalloc): the descriptor table goes to the library's fixed
     per-GPU array. Mesh dicts as for BatchPlan; at most
@@ -500,7 +501,8 @@ class BatchPlan:
         N.check(N.lib().fem_batch_plan_create(descs, len(meshes), _DT[dtype], ctypes.byref(self._plan)),
                 "fem_batch_plan_create")
 
-    def set_launch(self, waves_per_block=8, blocks_per_cu=0):
+    def set_launch(self, waves_per_block=N.BATCH_WAVES, blocks_per_cu=N.BATCH_BLOCKS_PER_CU):
+        """Launch shape of the plan; without arguments the one it starts with."""
         N.check(N.lib().fem_batch_plan_set_launch(self._plan, waves_per_block, blocks_per_cu),
                 "fem_batch_plan_set_launch")
 

@@ -2,7 +2,8 @@
 // persistent launch, optionally recorded into a HIP graph.
 //
 // The plan concatenates the meshes' element ranges into one list of tiles
-// (one tile = one workgroup's worth of elements, one element per lane) and
+// (one tile = one workgroup's worth of elements, one element per lane or 16
+// bytes of every row per lane, batch_vec) and
 // stores, per tile, the index of its mesh. Each persistent workgroup takes a
 // fixed contiguous run of tiles, so there is no work counter to reset between
 // launches and the assignment is the same on every replay. The workgroup
@@ -39,6 +40,9 @@ __device__ __forceinline__ void batch_element(const BatchMesh& M, int64_t e0) {
         load_rows_v<E::NBT>(static_cast<const Real*>(M.u), n, e, ru);
         load_rows_v<E::NCQ>(static_cast<const Real*>(M.coef), n, e, rcf);
         lane_residual<DIM, PHYS, RULE, Real>(rij, rdj, ru, rcf, rr);
+        // streaming stores, also at odd words: 64 meshes, 1.29 GB in FP32 234 us, 250
+        // with plain ones, 2.59 GB in FP64 467 and 498 (16 meshes of 185 and 370 MB the
+        // same and 67 and 64)
         store_rows_v<E::NBT, true>(static_cast<Real*>(M.out), n, e, rr);
     });
 }
@@ -126,8 +130,10 @@ struct fem_batch_plan {
     int64_t n_tiles = 0;
     int64_t n_elem_total = 0;
     int vec = 1;                 // elements per lane
-    int waves_per_block = 4;   // measured on MI355X: one tile per workgroup beats
-    int blocks_per_cu = 0;     // persistent grids
+    // One tile per workgroup beats persistent grids. Four waves: FP32, 64 meshes
+    // 234 us, 236 with eight, 8 meshes 41.7 and 44.0; FP64 467 and 474, 85 and 87.
+    int waves_per_block = 4;
+    int blocks_per_cu = 0;
     BatchMesh* d_meshes = nullptr;
     int32_t* d_tile_mesh = nullptr;   // mesh index of every tile
     int64_t tile_mesh_cap = 0;        // elements allocated in d_tile_mesh

@@ -234,3 +234,24 @@ def test_assembly_component_split(dim, nc, dtype, n_vert):
     F = plan.assemble(dev(R, dtype), nc).cpu().numpy()
     assert np.array_equal(F, oracle.assemble(dim, nc, n_vert, conn, R))
     plan.close()
+
+
+# rows above 32 slots: a few among short ones, which the whole wave sorts one after
+# the other (at the edges of 32, 64 and 256 entries), several in one group, and
+# groups of wide rows only, where every lane sorts its own
+@pytest.mark.parametrize("dim", [2, 3])
+@pytest.mark.parametrize("n_elem,n_vert,stars", [(300, 129, (32,)), (300, 129, (33,)), (300, 129, (64,)), (300, 129, (65, 200)),
+                                                 (900, 400, (255, 128, 129, 40)), (3000, 70, (100,)), (2000, 129, (200, 33)),
+                                                 (300, 64, (90, 90, 90))])
+def test_assembly_wide_rows(dim, n_elem, n_vert, stars):
+    rng = np.random.default_rng(n_elem + sum(stars))
+    hubs = rng.permutation(min(n_vert, 64))[:len(stars)]    # all in the first group of 64 vertices
+    conn = rng.choice(np.setdiff1d(np.arange(n_vert), hubs), size=(n_elem, dim + 1)).astype(np.int32)
+    for hub, star in zip(hubs, stars):
+        rows = rng.permutation(n_elem)[:star]
+        conn[rows, rng.integers(0, dim + 1, star)] = hub
+    R = rng.normal(size=((dim + 1) * 2, n_elem))
+    plan = api.AssemblyPlan(dev(conn, torch.int32), n_vert)
+    F = plan.assemble(dev(R, torch.float64), 2).cpu().numpy()
+    assert np.array_equal(F, oracle.assemble(dim, 2, n_vert, conn, R))
+    plan.close()

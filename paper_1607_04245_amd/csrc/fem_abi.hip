@@ -480,7 +480,13 @@ fem_status fem_integrate_residual_gather(int dim, int physics, int rule, int coe
     const fem_tuning t = get_tuning(FEM_OP_RESIDUAL_GATHER, dim, physics, rule, dtype);
     MeshArgs a{n_elem, n_vert, coords, conn, u_vertex, coef, elem_vec, inv_j, det_j, counts};
     Launch l = make_tile_launch(t, n_elem, static_cast<hipStream_t>(stream));
-    l.stream_out = whole_lines(n_elem, dtype == FEM_F32 ? 4 : 8, {elem_vec, inv_j, det_j});
+    // Three rows of a scalar form on triangles stream at odd words too, from 20 MiB on
+    // (us streaming and plain: FP32, 1,000,003 triangles 11.9 and 11.2, 2,000,011 19.5
+    // and 20.9, 3,000,017 28.6 and 29.7; FP64, 1,000,003 the same, 3,000,017 41.4 and
+    // 44.0)
+    const size_t word = dtype == FEM_F32 ? 4 : 8;
+    const bool few = dim == 2 && physics != FEM_ELASTICITY && n_elem * (int64_t)word * 3 >= (int64_t)20 << 20;
+    l.stream_out = few || whole_lines(n_elem, word, {elem_vec, inv_j, det_j});
     hipError_t e = launch_residual_gather(dim, physics, rule, coef_space, dtype, a, l);
     return e == hipSuccess ? FEM_OK : hip_fail(e, "fem_integrate_residual_gather launch");
 }

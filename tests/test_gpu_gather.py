@@ -150,3 +150,20 @@ def test_autotune_gather_op():
     R = gather(wl, torch.float32, cg, mg.COEF_QUAD)
     ref, ref_abs, _, _ = oracle_reference(wl, torch.float32, coef=cf)
     assert_close(R.cpu().numpy(), ref, ref_abs, torch.float32, "after autotune")
+
+
+# three rows of a scalar form on triangles stream from 20 MiB of output on
+@pytest.mark.parametrize("dtype,n", [(torch.float32, 1747626), (torch.float32, 1747627), (torch.float64, 873813),
+                                     (torch.float64, 873814)])
+def test_gather_streams_bitwise(dtype, n):
+    rng = torch.Generator("cuda").manual_seed(n)
+    nv = 5000
+    coords = torch.rand((nv, 2), generator=rng, device="cuda", dtype=torch.float64)
+    conn = torch.randint(0, nv, (n, 3), generator=rng, device="cuda", dtype=torch.int32)
+    u = torch.rand((nv, 1), generator=rng, device="cuda", dtype=torch.float64).to(dtype)
+    coef = torch.rand((1, 3, n), generator=rng, device="cuda", dtype=torch.float64).to(dtype) + 0.5
+    got = api.fem_integrate_residual_gather(2, mg.LAPLACE, mg.RULE_TRI3, coords, conn, u, coef)
+    for lo, hi in ((0, 1000), (n // 2, n // 2 + 1027), (n - 1001, n)):
+        part = api.fem_integrate_residual_gather(2, mg.LAPLACE, mg.RULE_TRI3, coords, conn[lo:hi].contiguous(), u,
+                                                 coef[..., lo:hi].contiguous())
+        assert torch.equal(got[:, lo:hi].nan_to_num(nan=7.0), part.nan_to_num(nan=7.0))

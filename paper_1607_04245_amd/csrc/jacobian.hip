@@ -223,13 +223,17 @@ __device__ __forceinline__ void mass_matrix(const Real* __restrict__ coef, int64
 // Calls f(rule constant, space constant) for the element's (rule, space):
 // order 1 takes the degree-2 rule or the centroid, order 2 the degree-2 or
 // the degree-4 rule. The host validates the pair; the arguments are uniform
-// over the grid, so the branch is scalar.
+// over the grid, so the branch is scalar. With one point, point values and a
+// constant are the same words and the same code, so they take one branch: of two
+// branches alike the compiler kept one and lost the other's |J| on its way there (P1
+// mass matrices, kernels that deal out no basis functions).
 template <int DIM, int ORDER, typename F>
 __device__ __forceinline__ void with_scheme(int rule, int space, const F& f) {
     constexpr int LOW = DIM == 2 ? FEM_RULE_TRI3 : FEM_RULE_TET4;
     constexpr int OTHER = ORDER == 1 ? FEM_RULE_CENTROID : (DIM == 2 ? FEM_RULE_TRI6 : FEM_RULE_TET11);
     auto by_space = [&](auto rule_c) {
-        if (space == FEM_COEF_QUAD) f(rule_c, std::integral_constant<int, FEM_COEF_QUAD>());
+        constexpr bool one_point = RuleBary<DIM, decltype(rule_c)::value>::NQ == 1;
+        if (!one_point && space == FEM_COEF_QUAD) f(rule_c, std::integral_constant<int, FEM_COEF_QUAD>());
         else if (space == FEM_COEF_P1) f(rule_c, std::integral_constant<int, FEM_COEF_P1>());
         else f(rule_c, std::integral_constant<int, FEM_COEF_P0>());
     };

@@ -266,9 +266,12 @@ static int64_t row_words(int dim, int phys, int rule, int space, int order, int 
 //    wave's edge meet in the L2 that neighbouring workgroups share: P1 FP32 0.82 at
 //    100 MB, 0.73 at 300, P2 FP32 0.72 and 0.67. (XCD by XCD 0.81 and 0.77 for P1, 1 %
 //    faster up to 100 MB, 2 to 7 % slower from 400 on, except on P3 tets: FP32, 200
-//    MB 0.63 and in runs 0.64, 900 MB 0.76 and 0.79.) P1 on FP64 triangles, where a
-//    wave's row has but two shared lines in five, streams from 544 MiB on (750 MB:
-//    0.96 of the first version's time, in runs 1.00; FP64 tets 0.80 and 0.79).
+//    MB 0.63 and in runs 0.64, 900 MB 0.76 and 0.79. P2 below 384 MiB goes XCD by XCD
+//    too: runs are 2 % faster over 60 to 380 MB, but not evenly, and 230 MB is 4 to 8 %
+//    slower: 3D Laplacian FP64, 700,001 tets 43.4 us, 40.3 XCD by XCD.) P1 on FP64
+//    triangles, where a wave's row has but two shared lines in five, streams from 544
+//    MiB on (750 MB: 0.96 of the first version's time, in runs 1.00; FP64 tets 0.80 and
+//    0.79).
 //  - Whole lines that the 256 MB last-level cache can hold in part: plain stores in
 //    runs. Residuals: P1 0.97 at 130 to 300 MB, 0.99 at 450, 1.04 at 540; P2 0.97, 0.99
 //    (3D elasticity 1.08) and 1.05; P3 0.98, 1.05 and 1.07. Adjoints: P1 0.97, 0.95 and
@@ -287,7 +290,8 @@ static void set_rows(Launch& l, bool whole, int dim, int dtype, int64_t bytes, i
     const int64_t low = order == 1 ? 0 : order == 3 && dim == 3 ? 128 : 64;
     const int64_t high = !adjoint && (order == 1 || dim == 2) ? 448 : 416;
     l.stream_out = whole ? stream || mib < low || mib >= high : order == 1 && dim == 2 && dtype == FEM_F64 && mib >= 544;
-    l.order = l.stream_out ? kOrderLaunch : !whole && order == 3 && dim == 3 ? kOrderXcd : kOrderRuns;
+    const bool xcd = !whole && (order == 2 ? mib < 384 : order == 3 && dim == 3);
+    l.order = l.stream_out ? kOrderLaunch : xcd ? kOrderXcd : kOrderRuns;
 }
 
 // Built-in configuration of the P1 lane kernels for n elements. Rows at odd words

@@ -19,7 +19,8 @@
 // accumulation registers; 209, and 512 with spills to memory before): 131 ->
 // 112 us and 310 -> 237 us at 600,032 tets (floors 109 and 219). Rows at odd words,
 // 600,011 tets: residual 152 -> 73 and 219 -> 168 us, adjoint 225 -> 137 and 354 ->
-// 259 us, most of it by their stores and workgroup order.
+// 259 us, most of it by their stores and workgroup order. 1000 tets, a wave's own
+// latency with the call: residual 10.0 -> 8.3 and 11.8 -> 8.8 us.
 #include "fem_internal.hpp"
 #include "p3_device.hpp"
 

@@ -13,7 +13,7 @@ namespace femq {
 
 template <int DIM, int PHYS, int RULE, typename Real, int V, bool STREAM_OUT>
 __global__ void __launch_bounds__(512)
-backward_lane_kernel(int64_t n, int order, const Real* __restrict__ inv_j, const Real* __restrict__ det_j,
+backward_lane_kernel(int64_t n, int place, const Real* __restrict__ inv_j, const Real* __restrict__ det_j,
                      const Real* __restrict__ u, const Real* __restrict__ coef,
                      const Real* __restrict__ w, Real* __restrict__ du, Real* __restrict__ dcoef) {
     using E = Elem<DIM, PHYS, RULE>;
@@ -21,7 +21,7 @@ backward_lane_kernel(int64_t n, int order, const Real* __restrict__ inv_j, const
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     const bool want_du = du != nullptr;
     const bool want_dc = dcoef != nullptr;
-    for (int64_t ch = row_block<STREAM_OUT>(order) * blockDim.x + threadIdx.x; ch < nchunk; ch += stride) {
+    for (int64_t ch = element_block<STREAM_OUT>(place) * blockDim.x + threadIdx.x; ch < nchunk; ch += stride) {
         for_chunk<V>(ch * V, n, [&](auto width, int64_t e) {
             constexpr int W = decltype(width)::value;
             Real rij[E::NG][W], rdj[1][W], rw[E::NBT][W];
@@ -70,7 +70,7 @@ static hipError_t launch_v(const BackwardArgs& a, const Launch& l) {
         constexpr int V = decltype(vec_c)::value;
         const auto k = l.stream_out ? backward_lane_kernel<DIM, PHYS, RULE, Real, V, true>
                                : backward_lane_kernel<DIM, PHYS, RULE, Real, V, false>;
-        hipLaunchKernelGGL(k, dim3(l.grid), dim3(l.block), 0, l.stream, a.n, l.order, ij, dj, u, cf, w, du, dc);
+        hipLaunchKernelGGL(k, dim3(l.grid), dim3(l.block), 0, l.stream, a.n, l.place(), ij, dj, u, cf, w, du, dc);
     };
     switch (l.vec) {
     case 1: go(std::integral_constant<int, 1>()); break;

@@ -257,7 +257,7 @@ static int64_t row_words(int dim, int phys, int rule, int space, int order, int 
     return dim * dim + 1 + (int64_t)n_closure * nb * nc + (int64_t)n_coef_sets * m * nw;
 }
 
-// Stores and workgroup order of a launch over `bytes` of rows of order-k elements;
+// Stores and workgroup order of a launch over rows of order-k elements, pitch bytes apart;
 // whole: every output row starts on a 128-byte line. Runs: 16 consecutive workgroups
 // per XCD. One MI355X, inputs rotating through more than the last-level cache holds;
 // times relative to streaming stores in launch order unless said otherwise, means
@@ -277,34 +277,57 @@ static int64_t row_words(int dim, int phys, int rule, int space, int order, int 
 //    (3D elasticity 1.08) and 1.05; P3 0.98, 1.05 and 1.07. Adjoints: P1 0.97, 0.95 and
 //    1.05, P2 0.97, 1.03 and 1.07, P3 0.97, 0.98 and 1.09. XCD by XCD, each XCD writing
 //    its own eighth of every row, is 3 % slower at 400 MB.
-//  - Whole lines above those limits, and below 64 MiB (128 on P3 tets), where plain
-//    stores push the inputs out (P3 tets, 60 MB: FP32 0.85 of the first version's time
-//    streamed, 0.91 plain; FP64 0.78 and 0.86): streaming stores in launch order. XCD by
-//    XCD they are 7 % slower at 700 MB.
+//  - Whole lines above those limits, and below 64 MiB on P2 and 128 on P3 tets, where
+//    plain stores push the inputs out (P3 tets, 60 MB: FP32 0.85 of the first version's
+//    time streamed, 0.91 plain; FP64 0.78 and 0.86; P2 3D elasticity, 40 MB, 16 % faster
+//    streamed; triangles at 10 to 66 MB 3 % slower): streaming stores in launch order.
+//    XCD by XCD they are 7 % slower at 700 MB.
 //  - `stream` asks for that at any size, where plain stores gain nothing: P3
-//    elasticity residuals, whose 20 or 60 rows leave in one burst after a long element
-//    (3D FP64, 230 MB: 33 us and 37; 2D: 43 and 48), and P1 residuals of scalar forms
-//    on FP64 tets, 4 rows out of 22 (230 MB: 37.8 and 39.0 us).
-static void set_rows(Launch& l, bool whole, int dim, int dtype, int64_t bytes, int order, bool adjoint, bool stream = false) {
-    const int64_t mib = bytes >> 20;
-    const int64_t low = order == 1 ? 0 : order == 3 && dim == 3 ? 128 : 64;
+//    elasticity residuals on tets and on FP64 triangles, whose 20 or 60 rows leave in
+//    one burst after a long element (3D FP64, 230 MB: 33 us and 37; 2D: 43 and 48; FP32
+//    triangles 170 MB 32.0 and 29.7), and P1 residuals of scalar forms on FP64 tets, 4
+//    rows out of 22 (230 MB: 37.8 and 39.0 us).
+//  - Rows a multiple of 8 MiB apart (P3: 4), as with a power of two of elements, meet in
+//    the same memory channels; there the XCDs stay apart, each in its own eighth of the
+//    rows, streaming from 512 MiB on. 2D elasticity FP32, 2^22 triangles (386 MB) 65.6 us
+//    in runs, 59.8 XCD by XCD; 3D Laplacian FP64, 2^21 tets (369 MB) 71 streaming, 56; 3D
+//    elasticity FP64 (705 MB) 126 streaming in launch order, 112 XCD by XCD. (An odd
+//    multiple of 2 MiB: the rules above.)
+static void set_rows(Launch& l, bool whole, int dim, int dtype, int64_t pitch, int64_t rows, int order, bool adjoint,
+                     bool stream = false) {
+    const int64_t mib = pitch * rows >> 20;
+    if (whole && pitch % ((int64_t)(order == 3 ? 4 : 8) << 20) == 0) {
+        l.stream_out = mib >= 512;
+        l.order = order < 3 || mib >= 192 ? kOrderXcd : kOrderRuns;
+        return;
+    }
+    const int64_t low = order == 1 || dim == 2 ? 0 : order == 3 ? 128 : 64;
     const int64_t high = !adjoint && (order == 1 || dim == 2) ? 448 : 416;
-    l.stream_out = whole ? stream || mib < low || mib >= high : order == 1 && dim == 2 && dtype == FEM_F64 && mib >= 544;
     const bool xcd = !whole && (order == 2 ? mib < 384 : order == 3 && dim == 3);
+    if (order == 1 && pitch % ((int64_t)4 << 20) == 0) stream = false;   // 524,288 tets 18.8 us, 16.8 plain
+    l.stream_out = whole ? stream || mib < low || mib >= high : order == 1 && dim == 2 && dtype == FEM_F64 && mib >= 544;
     l.order = l.stream_out ? kOrderLaunch : xcd ? kOrderXcd : kOrderRuns;
 }
 
-// Built-in configuration of the P1 lane kernels for n elements. Rows at odd words
-// take four waves per workgroup, and from six waves of 16-byte lanes per SIMD on in
-// FP32 four elements per lane and one wave, so that a wave shares 2 of its 9 lines
-// with its neighbours and not 2 of 3: 3D Laplacian, 2,272,267 tets 36.8 us with one
-// element per lane, 35.0 with four, 3D elasticity, 1,784,843 tets 58.9 and 53.7; but
-// the adjoint of the 3D Laplacian on 735,243 tets 17.6 and 19.5. (FP64, where 16 bytes
-// are two elements: the same.)
-static fem_tuning p1_tuning(const fem_tuning& t, int dtype, int64_t n, bool whole) {
-    if (whole) return t;
-    if (dtype == FEM_F32 && n >= (int64_t)4 * 64 * 6144) return fem_tuning{FEM_STRATEGY_LANE, 4, 1, 0};
-    return fem_tuning{FEM_STRATEGY_LANE, 1, 4, 0};
+// Built-in configuration of the P1 lane kernels for n elements, `bytes` of rows.
+//  - Whole lines: the default; rows a multiple of 4 MiB apart take four waves in FP64
+//    too (2^21 tets, 3D Laplacian 61.5 us with one, 56.3 with four, adjoint 82.1, 77.3).
+//  - Rows at odd words, but on 16 bytes (even: a count and arrays that allow it): 16
+//    bytes per lane and one wave, so that a wave shares 2 of its 9 lines with its
+//    neighbours and not 2 of 3, where that leaves five waves per CU and the rows are
+//    more than the caches of the XCDs hold: FP32, 3D Laplacian, 500,004 tets 8.7 us, 9.1
+//    with one element per lane, adjoint 11.2 and 12.6, 2,840,580 tets 43.1 and 45.1; FP64,
+//    2D elasticity, 420,868 triangles 12.2 and 12.7; but FP32 2D Laplacian, 500,004
+//    triangles (28 MB) 7.1 and 6.4.
+//  - Off 16 bytes each such access is split: only from six waves per SIMD on in FP32
+//    (2,272,267 tets 36.8 us with one element per lane, 35.0 with four; but the adjoint on
+//    735,243 tets 17.6 and 19.5; FP64 the same), else one element and four waves.
+static fem_tuning p1_tuning(const fem_tuning& t, int dtype, int64_t n, int64_t bytes, bool whole, bool even) {
+    const int word = dtype == FEM_F32 ? 4 : 8, vec = 16 / word;
+    const fem_tuning one{FEM_STRATEGY_LANE, 1, 4, 0}, wide{FEM_STRATEGY_LANE, vec, 1, 0};
+    if (whole) return n * word % ((int64_t)4 << 20) == 0 ? one : t;
+    if (even) return n >= (int64_t)vec * 64 * 1280 && bytes >= (int64_t)32 << 20 ? wide : one;
+    return dtype == FEM_F32 && n >= (int64_t)vec * 64 * 6144 ? wide : one;
 }
 
 static Launch make_launch(const fem_tuning& t, int64_t work_items, int vec, hipStream_t s) {
@@ -435,9 +458,11 @@ fem_status fem_integrate_residual(int dim, int physics, int rule, int coef_space
     } else {
         const size_t word = dtype == FEM_F32 ? 4 : 8;
         const bool whole = whole_lines(n_elem, word, {elem_vec});
-        if (!chosen) t = p1_tuning(t, dtype, n_elem, whole);
+        const int64_t pitch = n_elem * (int64_t)word, rows = row_words(dim, physics, rule, coef_space, 1, 2, 1);
+        if (!chosen) t = p1_tuning(t, dtype, n_elem, pitch * rows, whole,
+                                   whole_lines(n_elem, word, {inv_j, det_j, u, coef, elem_vec}, 16));
         Launch l = make_launch(t, (n_elem + t.vec - 1) / t.vec, t.vec, static_cast<hipStream_t>(stream));
-        set_rows(l, whole, dim, dtype, n_elem * (int64_t)word * row_words(dim, physics, rule, coef_space, 1, 2, 1), 1, false,
+        set_rows(l, whole, dim, dtype, pitch, rows, 1, false,
                  dim == 3 && dtype == FEM_F64 && physics != FEM_ELASTICITY);
         e = launch_residual_lane(dim, physics, rule, coef_space, dtype, a, l);
     }
@@ -511,12 +536,14 @@ fem_status fem_integrate_residual_backward(int dim, int physics, int rule, int c
     fem_tuning t = get_tuning(FEM_OP_BACKWARD, dim, physics, rule, dtype, &chosen);
     const size_t word = dtype == FEM_F32 ? 4 : 8;
     const bool whole = whole_lines(n_elem, word, {du, dcoef});
-    if (!chosen) t = p1_tuning(t, dtype, n_elem, whole);
+    const int64_t pitch = n_elem * (int64_t)word;
+    const int64_t rows = row_words(dim, physics, rule, coef_space, 1, (du ? 2 : 1) + (dcoef ? 1 : 0),
+                                   (du ? 1 : 0) + (dcoef ? 1 : 0));
+    if (!chosen) t = p1_tuning(t, dtype, n_elem, pitch * rows, whole,
+                               whole_lines(n_elem, word, {inv_j, det_j, u, coef, w, du, dcoef}, 16));
     BackwardArgs a{n_elem, inv_j, det_j, u, coef, w, du, dcoef};
     Launch l = make_launch(t, (n_elem + t.vec - 1) / t.vec, t.vec, static_cast<hipStream_t>(stream));
-    set_rows(l, whole, dim, dtype, n_elem * (int64_t)word *
-                           row_words(dim, physics, rule, coef_space, 1, (du ? 2 : 1) + (dcoef ? 1 : 0),
-                                     (du ? 1 : 0) + (dcoef ? 1 : 0)), 1, true);
+    set_rows(l, whole, dim, dtype, pitch, rows, 1, true);
     hipError_t e = launch_backward_lane(dim, physics, rule, coef_space, dtype, a, l);
     return e == hipSuccess ? FEM_OK : hip_fail(e, "fem_integrate_residual_backward launch");
 }
@@ -538,7 +565,7 @@ fem_status fem_integrate_residual_p2(int dim, int physics, int rule, int coef_sp
     Launch l = make_launch(t, n_elem, 1, static_cast<hipStream_t>(stream));
     const size_t word = dtype == FEM_F32 ? 4 : 8;
     set_rows(l, whole_lines(n_elem, word, {elem_vec}), dim, dtype,
-             n_elem * (int64_t)word * row_words(dim, physics, rule, coef_space, 2, 2, 1), 2, false);
+             n_elem * (int64_t)word, row_words(dim, physics, rule, coef_space, 2, 2, 1), 2, false);
     hipError_t e = launch_residual_p2(dim, physics, rule, coef_space, dtype, a, l);
     return e == hipSuccess ? FEM_OK : hip_fail(e, "fem_integrate_residual_p2 launch");
 }
@@ -573,7 +600,8 @@ fem_status fem_integrate_residual_p3(int dim, int physics, int rule, int coef_sp
         Launch l = make_launch(t, n_elem, 1, static_cast<hipStream_t>(stream));
         const size_t word = dtype == FEM_F32 ? 4 : 8;
         set_rows(l, whole_lines(n_elem, word, {elem_vec}), dim, dtype,
-                 n_elem * (int64_t)word * row_words(dim, physics, rule, coef_space, 3, 2, 1), 3, false, physics == FEM_ELASTICITY);
+                 n_elem * (int64_t)word, row_words(dim, physics, rule, coef_space, 3, 2, 1), 3, false,
+                 physics == FEM_ELASTICITY && (dim == 3 || dtype == FEM_F64));
         e = launch_residual_p3(dim, physics, coef_space, dtype, a, l);
     }
     return e == hipSuccess ? FEM_OK : hip_fail(e, "fem_integrate_residual_p3 launch");
@@ -596,7 +624,7 @@ fem_status fem_integrate_residual_p2_backward(int dim, int physics, int rule, in
     Launch l = make_launch(t, n_elem, 1, static_cast<hipStream_t>(stream));
     const size_t word = dtype == FEM_F32 ? 4 : 8;
     set_rows(l, whole_lines(n_elem, word, {du, dcoef}), dim, dtype,
-             n_elem * (int64_t)word * row_words(dim, physics, rule, coef_space, 2, (du ? 2 : 1) + (dcoef ? 1 : 0), (du ? 1 : 0) + (dcoef ? 1 : 0)), 2, true);
+             n_elem * (int64_t)word, row_words(dim, physics, rule, coef_space, 2, (du ? 2 : 1) + (dcoef ? 1 : 0), (du ? 1 : 0) + (dcoef ? 1 : 0)), 2, true);
     hipError_t e = launch_backward_p2(dim, physics, rule, coef_space, dtype, a, l);
     return e == hipSuccess ? FEM_OK : hip_fail(e, "fem_integrate_residual_p2_backward launch");
 }
@@ -618,7 +646,7 @@ fem_status fem_integrate_residual_p3_backward(int dim, int physics, int rule, in
     Launch l = make_launch(t, n_elem, 1, static_cast<hipStream_t>(stream));
     const size_t word = dtype == FEM_F32 ? 4 : 8;
     set_rows(l, whole_lines(n_elem, word, {du, dcoef}), dim, dtype,
-             n_elem * (int64_t)word * row_words(dim, physics, rule, coef_space, 3, (du ? 2 : 1) + (dcoef ? 1 : 0), (du ? 1 : 0) + (dcoef ? 1 : 0)), 3, true);
+             n_elem * (int64_t)word, row_words(dim, physics, rule, coef_space, 3, (du ? 2 : 1) + (dcoef ? 1 : 0), (du ? 1 : 0) + (dcoef ? 1 : 0)), 3, true);
     hipError_t e = launch_backward_p3(dim, physics, coef_space, dtype, a, l);
     return e == hipSuccess ? FEM_OK : hip_fail(e, "fem_integrate_residual_p3_backward launch");
 }

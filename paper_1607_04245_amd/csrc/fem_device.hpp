@@ -514,6 +514,16 @@ __device__ __forceinline__ int64_t row_block(int order) {
     else return row_block(order);
 }
 
+// The same for the integrate kernels and their adjoints (Launch::place): a streaming
+// launch may run XCD by XCD too, and is told how many workgroups an XCD takes (0:
+// launch order), so that it waits for no second load of its grid.
+template <bool STREAM_OUT>
+__device__ __forceinline__ int64_t element_block(int place) {
+    const uint32_t b = blockIdx.x;
+    if constexpr (STREAM_OUT) return place == 0 ? b : b % kXcds * (uint32_t)place + b / kXcds;
+    else return row_block(place);
+}
+
 // Words e of N consecutive rows.
 template <int N, typename Real>
 __device__ __forceinline__ void load_rows(const Real* __restrict__ p, int64_t n, int64_t e, Real (&x)[N]) {

@@ -64,6 +64,9 @@ struct Launch {
     int max_grid = 1 << 22;  // workgroups that the configuration allows
     bool stream_out = true;  // output rows leave with streaming stores (row_st)
     int order = 0;           // place of each workgroup, RowOrder (row_block)
+    // The order as element_block takes it. Streaming launches run XCD by XCD only
+    // where the XCDs take the same number of workgroups.
+    int place() const { return !stream_out ? order : order == kOrderXcd && grid % 8 == 0 ? grid / 8 : 0; }
 };
 
 // Workgroups for one pass over so many lanes, and the grid: no more of them than
@@ -90,11 +93,11 @@ inline int matrix_parts(const Launch& l, int64_t lanes, int rows, int64_t want) 
 constexpr int64_t kMatrixWaves = 640;   // P1 and P2
 
 // Whether rows of n words in each of the given arrays (NULL ones are skipped)
-// all start on a 128-byte cache line.
-inline bool whole_lines(int64_t n, size_t word, std::initializer_list<const void*> arrays) {
-    if ((size_t)n * word % 128 != 0) return false;
+// all start on a multiple of `align` bytes: a 128-byte cache line.
+inline bool whole_lines(int64_t n, size_t word, std::initializer_list<const void*> arrays, size_t align = 128) {
+    if ((size_t)n * word % align != 0) return false;
     for (const void* p : arrays)
-        if (reinterpret_cast<uintptr_t>(p) % 128 != 0) return false;
+        if (reinterpret_cast<uintptr_t>(p) % align != 0) return false;
     return true;
 }
 

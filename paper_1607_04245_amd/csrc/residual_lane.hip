@@ -19,13 +19,13 @@ namespace femq {
 
 template <int DIM, int PHYS, int RULE, typename Real, int V, bool STREAM_OUT>
 __global__ void __launch_bounds__(512)
-residual_lane_kernel(int64_t n, int order, const Real* __restrict__ inv_j, const Real* __restrict__ det_j,
+residual_lane_kernel(int64_t n, int place, const Real* __restrict__ inv_j, const Real* __restrict__ det_j,
                      const Real* __restrict__ u, const Real* __restrict__ coef,
                      Real* __restrict__ out) {
     using E = Elem<DIM, PHYS, RULE>;
     const int64_t nchunk = (n + V - 1) / V;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t ch = row_block<STREAM_OUT>(order) * blockDim.x + threadIdx.x; ch < nchunk; ch += stride) {
+    for (int64_t ch = element_block<STREAM_OUT>(place) * blockDim.x + threadIdx.x; ch < nchunk; ch += stride) {
         for_chunk<V>(ch * V, n, [&](auto width, int64_t e) {
             constexpr int W = decltype(width)::value;
             Real rij[E::NG][W], rdj[1][W], ru[E::NBT][W], rcf[E::NCQ][W], rr[E::NBT][W];
@@ -50,7 +50,7 @@ static hipError_t launch_v(const ResidualArgs& a, const Launch& l) {
         constexpr int V = decltype(vec_c)::value;
         const auto k = l.stream_out ? residual_lane_kernel<DIM, PHYS, RULE, Real, V, true>
                                : residual_lane_kernel<DIM, PHYS, RULE, Real, V, false>;
-        hipLaunchKernelGGL(k, dim3(l.grid), dim3(l.block), 0, l.stream, a.n, l.order, ij, dj, u, cf, out);
+        hipLaunchKernelGGL(k, dim3(l.grid), dim3(l.block), 0, l.stream, a.n, l.place(), ij, dj, u, cf, out);
     };
     switch (l.vec) {
     case 1: go(std::integral_constant<int, 1>()); break;

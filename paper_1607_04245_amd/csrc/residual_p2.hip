@@ -15,11 +15,11 @@ namespace femq {
 
 template <int DIM, int PHYS, int RULE, int SPACE, typename Real, bool STREAM_OUT>
 __global__ void __launch_bounds__(256)
-residual_p2_kernel(int64_t n, int order, const Real* __restrict__ inv_j, const Real* __restrict__ det_j,
+residual_p2_kernel(int64_t n, int place, const Real* __restrict__ inv_j, const Real* __restrict__ det_j,
                    const Real* __restrict__ u, const Real* __restrict__ coef, Real* __restrict__ out) {
     using E = ElemP2<DIM, PHYS, RULE, SPACE>;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t e = row_block<STREAM_OUT>(order) * blockDim.x + threadIdx.x; e < n; e += stride) {
+    for (int64_t e = element_block<STREAM_OUT>(place) * blockDim.x + threadIdx.x; e < n; e += stride) {
         Real ij[E::NG], uu[E::NBT], cf[E::NCQ], r[E::NBT];
         load_rows<E::NG>(inv_j, n, e, ij);
         const Real dj = row_ld(det_j + e);
@@ -34,12 +34,12 @@ residual_p2_kernel(int64_t n, int order, const Real* __restrict__ inv_j, const R
 // skipped (wave-uniform flags), and u is read only for dcoef.
 template <int DIM, int PHYS, int RULE, int SPACE, typename Real, bool STREAM_OUT>
 __global__ void __launch_bounds__(256)
-backward_p2_kernel(int64_t n, int order, const Real* __restrict__ inv_j, const Real* __restrict__ det_j,
+backward_p2_kernel(int64_t n, int place, const Real* __restrict__ inv_j, const Real* __restrict__ det_j,
                    const Real* __restrict__ u, const Real* __restrict__ coef, const Real* __restrict__ w,
                    Real* __restrict__ du, Real* __restrict__ dcoef) {
     using E = ElemP2<DIM, PHYS, RULE, SPACE>;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t e = row_block<STREAM_OUT>(order) * blockDim.x + threadIdx.x; e < n; e += stride) {
+    for (int64_t e = element_block<STREAM_OUT>(place) * blockDim.x + threadIdx.x; e < n; e += stride) {
         Real ij[E::NG], ww[E::NBT];
         load_rows<E::NG>(inv_j, n, e, ij);
         const Real dj = row_ld(det_j + e);
@@ -69,7 +69,7 @@ static hipError_t launch_fwd(const ResidualArgs& a, const Launch& l) {
     const auto k = l.stream_out ? residual_p2_kernel<DIM, PHYS, RULE, SPACE, Real, true>
                            : residual_p2_kernel<DIM, PHYS, RULE, SPACE, Real, false>;
     hipLaunchKernelGGL(k, dim3(l.grid), dim3(l.block), 0, l.stream,
-                       a.n, l.order, static_cast<const Real*>(a.inv_j), static_cast<const Real*>(a.det_j),
+                       a.n, l.place(), static_cast<const Real*>(a.inv_j), static_cast<const Real*>(a.det_j),
                        static_cast<const Real*>(a.u), static_cast<const Real*>(a.coef), static_cast<Real*>(a.out));
     return hipGetLastError();
 }
@@ -79,7 +79,7 @@ static hipError_t launch_bwd(const BackwardArgs& a, const Launch& l) {
     const auto k = l.stream_out ? backward_p2_kernel<DIM, PHYS, RULE, SPACE, Real, true>
                            : backward_p2_kernel<DIM, PHYS, RULE, SPACE, Real, false>;
     hipLaunchKernelGGL(k, dim3(l.grid), dim3(l.block), 0, l.stream,
-                       a.n, l.order, static_cast<const Real*>(a.inv_j), static_cast<const Real*>(a.det_j),
+                       a.n, l.place(), static_cast<const Real*>(a.inv_j), static_cast<const Real*>(a.det_j),
                        static_cast<const Real*>(a.u), static_cast<const Real*>(a.coef), static_cast<const Real*>(a.w),
                        static_cast<Real*>(a.du), static_cast<Real*>(a.dcoef));
     return hipGetLastError();

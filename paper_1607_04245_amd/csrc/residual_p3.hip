@@ -73,12 +73,12 @@ __device__ __forceinline__ void tet_store(const Real* ij, const Real (&G)[11][NC
 
 template <int DIM, int PHYS, typename Real, bool STREAM_OUT>
 __global__ void __launch_bounds__(256)
-residual_p3_kernel(int64_t n, int order, int space, const Real* __restrict__ inv_j, const Real* __restrict__ det_j,
+residual_p3_kernel(int64_t n, int place, int space, const Real* __restrict__ inv_j, const Real* __restrict__ det_j,
                    const Real* __restrict__ u, const Real* __restrict__ coef, Real* __restrict__ out) {
     constexpr int RULE = DIM == 2 ? FEM_RULE_TRI6 : FEM_RULE_TET11;
     using E = ElemP3<DIM, PHYS, RULE, FEM_COEF_QUAD>;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t e = row_block<STREAM_OUT>(order) * blockDim.x + threadIdx.x; e < n; e += stride) {
+    for (int64_t e = element_block<STREAM_OUT>(place) * blockDim.x + threadIdx.x; e < n; e += stride) {
         Real ij[E::NG], uu[E::NBT], aq[E::NCQ];
         load_rows<E::NG>(inv_j, n, e, ij);
         const Real dj = row_ld(det_j + e);
@@ -104,14 +104,14 @@ residual_p3_kernel(int64_t n, int order, int space, const Real* __restrict__ inv
 // (uniform flags); u is read only for dcoef.
 template <int DIM, int PHYS, typename Real, bool STREAM_OUT>
 __global__ void __launch_bounds__(256)
-backward_p3_kernel(int64_t n, int order, int space, const Real* __restrict__ inv_j, const Real* __restrict__ det_j,
+backward_p3_kernel(int64_t n, int place, int space, const Real* __restrict__ inv_j, const Real* __restrict__ det_j,
                    const Real* __restrict__ u, const Real* __restrict__ coef, const Real* __restrict__ w,
                    Real* __restrict__ du, Real* __restrict__ dcoef) {
     constexpr int RULE = DIM == 2 ? FEM_RULE_TRI6 : FEM_RULE_TET11;
     using E = ElemP3<DIM, PHYS, RULE, FEM_COEF_QUAD>;
     using Q = RuleP2<DIM, RULE>;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t e = row_block<STREAM_OUT>(order) * blockDim.x + threadIdx.x; e < n; e += stride) {
+    for (int64_t e = element_block<STREAM_OUT>(place) * blockDim.x + threadIdx.x; e < n; e += stride) {
         Real ij[E::NG], ww[E::NBT];
         load_rows<E::NG>(inv_j, n, e, ij);
         const Real dj = row_ld(det_j + e);
@@ -334,7 +334,7 @@ static hipError_t launch_jac(int space, const JacobianArgs& a, const Launch& l) 
 template <int DIM, int PHYS, typename Real>
 static hipError_t launch_bwd(int space, const BackwardArgs& a, const Launch& l) {
     const auto k = l.stream_out ? backward_p3_kernel<DIM, PHYS, Real, true> : backward_p3_kernel<DIM, PHYS, Real, false>;
-    hipLaunchKernelGGL(k, dim3(l.grid), dim3(l.block), 0, l.stream, a.n, l.order, space,
+    hipLaunchKernelGGL(k, dim3(l.grid), dim3(l.block), 0, l.stream, a.n, l.place(), space,
                        static_cast<const Real*>(a.inv_j), static_cast<const Real*>(a.det_j),
                        static_cast<const Real*>(a.u), static_cast<const Real*>(a.coef), static_cast<const Real*>(a.w),
                        static_cast<Real*>(a.du), static_cast<Real*>(a.dcoef));
@@ -344,7 +344,7 @@ static hipError_t launch_bwd(int space, const BackwardArgs& a, const Launch& l) 
 template <int DIM, int PHYS, typename Real>
 static hipError_t launch_fwd(int space, const ResidualArgs& a, const Launch& l) {
     const auto k = l.stream_out ? residual_p3_kernel<DIM, PHYS, Real, true> : residual_p3_kernel<DIM, PHYS, Real, false>;
-    hipLaunchKernelGGL(k, dim3(l.grid), dim3(l.block), 0, l.stream, a.n, l.order, space,
+    hipLaunchKernelGGL(k, dim3(l.grid), dim3(l.block), 0, l.stream, a.n, l.place(), space,
                        static_cast<const Real*>(a.inv_j), static_cast<const Real*>(a.det_j),
                        static_cast<const Real*>(a.u), static_cast<const Real*>(a.coef), static_cast<Real*>(a.out));
     return hipGetLastError();

@@ -50,11 +50,21 @@ def _lanes(n, vec):
 def test_chosen_shape_at_odd_words(launches, call, op, dtype, waves, odd, n, offset):
     key = (3, mg.LAPLACE, mg.RULE_TET4)
     c = (call, *key, N.COEF_QUAD, dtype, n, offset)
-    whole, built_in, chosen = launches((call, *key, N.COEF_QUAD, dtype, 1 << 21, 0), c,
+    whole, built_in, chosen = launches((call, *key, N.COEF_QUAD, dtype, (1 << 21) - 32, 0), c,
                                        ("set", op, *key, dtype, N.STRATEGY_LANE, 1, waves, 0), c)
     assert (whole["args"][4], whole["block"]) == ("1", 64 * waves)
     assert (built_in["args"][4], built_in["block"]) == (str(odd[0]), 64 * odd[1])
     assert (chosen["args"][4], chosen["block"]) == ("1", 64 * waves) and chosen["grid"] == (_lanes(n, 64 * waves), 1)
+
+
+# rows at odd words, the arrays on 16 bytes: 16 bytes per lane from 1280 waves and 32
+# MiB of rows (22 of a tet's Laplacian) on
+@pytest.mark.parametrize("call", ["residual", "backward"])
+@pytest.mark.parametrize("dtype,n,vec", [(F32, 327676, 1), (F32, 400004, 4), (F32, 400002, 1),
+                                         (F64, 163838, 1), (F64, 220002, 2), (F64, 220001, 1)])
+def test_width_at_odd_words(launches, call, dtype, n, vec):
+    got, = launches((call, 3, mg.LAPLACE, mg.RULE_TET4, N.COEF_QUAD, dtype, n, 0))
+    assert (got["args"][4], got["block"]) == (str(vec), 64 if vec > 1 else 256)
 
 
 @pytest.mark.parametrize("order,op,rule", [(1, N.OP_JACOBIAN, mg.RULE_TET4), (2, N.OP_JACOBIAN_P2, mg.RULE_TET11),
@@ -90,13 +100,25 @@ def test_built_in_matrix_shapes(launches):
 # stores in runs, but FP64 triangles stream when large
 @pytest.mark.parametrize("dim,physics,dtype,n,offset,stream", [
     (3, mg.ELASTICITY, F32, 1 << 20, 0, 0), (3, mg.ELASTICITY, F32, 2796160, 0, 0), (3, mg.ELASTICITY, F32, 2796224, 0, 1),
-    (3, mg.LAPLACE, F64, 1 << 20, 0, 1), (2, mg.LAPLACE, F64, (1 << 22) - 32, 0, 0), (3, mg.ELASTICITY, F32, 2796224, 1, 0),
+    (3, mg.LAPLACE, F64, (1 << 20) - 32, 0, 1), (2, mg.LAPLACE, F64, (1 << 22) - 32, 0, 0), (3, mg.ELASTICITY, F32, 2796224, 1, 0),
     (3, mg.ELASTICITY, F64, 1 << 21, 1, 0), (2, mg.ELASTICITY, F64, 1 << 21, 1, 0), (2, mg.ELASTICITY, F64, 3100000, 1, 0),
     (2, mg.ELASTICITY, F64, 3100704, 1, 1)])
 def test_row_stores(launches, dim, physics, dtype, n, offset, stream):
     rule = mg.RULE_TRI3 if dim == 2 else mg.RULE_TET4
     got, = launches(("residual", dim, physics, rule, N.COEF_QUAD, dtype, n, offset))
     assert got["args"][5] == ("true" if stream else "false") and got["order"] == (0 if stream else 2)
+
+
+# rows a multiple of 8 MiB apart: XCD by XCD (an eighth of the workgroups each where
+# they stream, from 512 MiB of rows on); 4 MiB and an odd multiple of 2 are not that
+@pytest.mark.parametrize("dim,physics,dtype,n,stream,order", [
+    (3, mg.LAPLACE, F64, 1 << 20, 0, 1), (2, mg.ELASTICITY, F32, 1 << 22, 0, 1), (3, mg.ELASTICITY, F64, 1 << 21, 1, None),
+    (3, mg.ELASTICITY, F64, 3 << 20, 1, None), (3, mg.ELASTICITY, F32, 1 << 20, 0, 2), (3, mg.ELASTICITY, F32, 3 << 19, 0, 2)])
+def test_rows_far_apart(launches, dim, physics, dtype, n, stream, order):
+    rule = mg.RULE_TRI3 if dim == 2 else mg.RULE_TET4
+    got, = launches(("residual", dim, physics, rule, N.COEF_QUAD, dtype, n, 0))
+    assert got["args"][5] == ("true" if stream else "false") and got["block"] == 256
+    assert got["order"] == (got["grid"][0] // 8 if order is None else order)
 
 
 # shares of a tile's P1 and P2 matrices: no more than 640 waves, streaming at whole

@@ -676,7 +676,11 @@ fem_status fem_integrate_jacobian(int dim, int physics, int rule, int coef_space
     const size_t word = dtype == FEM_F32 ? 4 : 8;
     const bool whole = whole_lines(n_elem, word, {elem_mat});
     const bool by_xcd = !whole || (order == 1 && physics == FEM_ELASTICITY && n_elem * (int64_t)word >= (int64_t)4 << 20);
-    if (by_xcd && !chosen) t = fem_tuning{FEM_STRATEGY_LANE, 1, 4, 0};
+    // P2 scalar rows a multiple of 8 MiB apart take four waves too, from 512 MiB on (3D Laplacian
+    // FP64, 2^20 tets 200 us with one, 193 with four; 10^6 tets 190 either way).
+    const int64_t pitch = n_elem * (int64_t)word, nb = (dim + 1) * (dim + 2) / 2;
+    const bool apart = order == 2 && physics != FEM_ELASTICITY && pitch % ((int64_t)8 << 20) == 0 && pitch * nb * nb >= (int64_t)512 << 20;
+    if ((by_xcd || apart) && !chosen) t = fem_tuning{FEM_STRATEGY_LANE, 1, 4, 0};
     JacobianArgs a{n_elem, inv_j, det_j, coef, elem_mat};
     Launch l = make_launch(t, n_elem, 1, static_cast<hipStream_t>(stream));
     l.stream_out = whole;

@@ -129,3 +129,10 @@ def test_matrix_shares(launches, dtype, n, share):
     got, = launches(("jacobian", 3, mg.ELASTICITY, mg.RULE_TET11, N.COEF_QUAD, dtype, n, 0, 2))
     assert got["grid"] == (_lanes(n, 256), share)
     assert got["args"][4] == ("true" if n % 32 == 0 else "false")
+
+
+@pytest.mark.parametrize("dim,n,waves", [(3, 1 << 20, 4), (3, 1000000, 1), (2, 1 << 20, 1), (2, 1 << 21, 4)])
+def test_p2_matrix_waves(launches, dim, n, waves):
+    rule = mg.RULE_TRI6 if dim == 2 else mg.RULE_TET11
+    got, = launches(("jacobian", dim, mg.LAPLACE, rule, N.COEF_QUAD, F64, n, 0, 2))
+    assert got["block"] == 64 * waves

@@ -291,13 +291,14 @@ static int64_t row_words(int dim, int phys, int rule, int space, int order, int 
 //    the same memory channels; there the XCDs stay apart, each in its own eighth of the
 //    rows, streaming from 512 MiB on. 2D elasticity FP32, 2^22 triangles (386 MB) 65.6 us
 //    in runs, 59.8 XCD by XCD; 3D Laplacian FP64, 2^21 tets (369 MB) 71 streaming, 56; 3D
-//    elasticity FP64 (705 MB) 126 streaming in launch order, 112 XCD by XCD. (An odd
-//    multiple of 2 MiB: the rules above.)
+//    elasticity FP64 (705 MB) 126 streaming in launch order, 112 XCD by XCD. P3 residuals
+//    on tets stream from 448 MiB on (Laplacian FP64, 2^20 tets, 107 us plain, 101). An
+//    odd multiple of 2 MiB: the rules above.
 static void set_rows(Launch& l, bool whole, int dim, int dtype, int64_t pitch, int64_t rows, int order, bool adjoint,
                      bool stream = false) {
     const int64_t mib = pitch * rows >> 20;
     if (whole && pitch % ((int64_t)(order == 3 ? 4 : 8) << 20) == 0) {
-        l.stream_out = mib >= 512;
+        l.stream_out = mib >= (order == 3 && dim == 3 && !adjoint ? 448 : 512);
         l.order = order < 3 || mib >= 192 ? kOrderXcd : kOrderRuns;
         return;
     }

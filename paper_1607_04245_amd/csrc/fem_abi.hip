@@ -164,8 +164,8 @@ static fem_tuning default_tuning(int op, int dim, int phys, int rule, int dtype)
     if (op == FEM_OP_JACOBIAN) return fem_tuning{FEM_STRATEGY_LANE, 1, f32 && phys != FEM_ELASTICITY ? 2 : 1, 0};
     // P3: the 3D elements hold 20-60 closure and output words per lane, and
     // single-wave workgroups measured fastest there; 2D streams better with
-    // four. (The component split of 3D elasticity, 2^21 tets: FP32 274 us, the
-    // lane kernel 250; FP64 570 and 487.)
+    // four. (The component split of 3D elasticity, 2^21 tets: FP32 280 us, the
+    // lane kernel 242; FP64 584 and 485.)
     if (op == FEM_OP_RESIDUAL_P3 || op == FEM_OP_BACKWARD_P3) return fem_tuning{FEM_STRATEGY_LANE, 1, dim == 3 ? 1 : 4, 0};
     if (op == FEM_OP_JACOBIAN_P3) return fem_tuning{FEM_STRATEGY_LANE, 1, 4, 0};
     // P2 (the remaining ops of one element per lane): four waves (2D elasticity FP32,

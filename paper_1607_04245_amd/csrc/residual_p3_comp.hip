@@ -33,7 +33,7 @@
 // products g_v . f1_c are summed in rotated order, and the quadrature weight
 // scales lambda and mu instead of the flux). The lane kernel has since gained
 // from the point orbits of P3Tet, which the split does not use: 2^21 tets, FP32
-// 274 us against 250, FP64 570 against 487. In FP32 the split issues 131 M vector
+// 280 us against 242, FP64 584 against 485. In FP32 the split issues 131 M vector
 // instructions, and in FP64 three groups per CU (the LDS bound) keep fewer bytes
 // in flight than the lane kernel's single wave per SIMD with all its
 // element's loads issued at once.
